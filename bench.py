@@ -158,7 +158,7 @@ def bench_32k(torch, bd, synth, steps, warmup, reading=0):
             "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS, "traffic": recorded_traffic(dom),
             "flop_per_launch": kern[dom]["flop_per_launch"], "avg_launch_ms": kern[dom]["avg_ms"]}
     fwd_ms = kern["fwd_bf16"]["avg_ms"]
-    bwd_ms = sum(kern[k]["avg_ms"] for k in ("bwd_pre", "bwd_dkdv_bf16", "bwd_dq_bf16") if k in kern)
+    bwd_ms = sum(kern[k]["avg_ms"] for k in ("bwd_dkdv_bf16", "bwd_dq_bf16") if k in kern)
     res = {"ms_per_step": ms, "median_ms_per_step": median_ms, "fwd_ms": fwd_ms, "bwd_ms": bwd_ms,
            "wall_s": wall, "pairs_per_head": pairs, "flops": fl, "kernels": kern,
            "roofline": roof, "value": fl["total"] / (median_ms * 1e-3) / 1e12,

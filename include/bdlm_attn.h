@@ -217,6 +217,16 @@ bdlm_status bdlm_lse_merge_strided(int64_t batch, int64_t rows, int32_t heads, i
  * batch * len * heads exceeds 2^28 are rejected by bdlm_attn_bwd. */
 size_t bdlm_attn_bwd_workspace_bytes(const bdlm_problem* p, int32_t n_q, const bdlm_range* q_ranges);
 
+/* Workspace bytes with which bdlm_attn_bwd may also cut long dK/dV walks into
+ * chunks that run side by side (for calls with too few key tiles to fill the
+ * card): bdlm_attn_bwd_workspace_bytes() plus room for the chunks' partial
+ * sums, at most 256 MiB more; equal to it where cutting does not help.  The
+ * call takes either size.  The sums of a cut walk are added in a fixed order
+ * (results are reproducible), which is another order than in an uncut walk:
+ * dK and dV may differ from the smaller workspace's in the last bits. */
+size_t bdlm_attn_bwd_split_workspace_bytes(const bdlm_problem* p, int32_t n_q, const bdlm_range* q_ranges,
+                                           int32_t n_k, const bdlm_range* k_ranges);
+
 /*
  * Backward from the saved (final, merged) O and LSE (App. C fused backward;
  * eqs. eq:correctness-corrupted-gradient .. eq:correctness-query-gradient).

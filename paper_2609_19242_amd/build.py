@@ -17,8 +17,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libbdlm_attn.so")
 BUILD_DIR = os.path.join(HERE, "_build")
-SOURCES = ["api.cpp", "fwd_bf16.hip", "fwd_f32.hip", "merge.hip", "bwd_pre.hip", "bwd_bf16.hip", "bwd_dkdv.hip",
-           "bwd_dq.hip", "bwd_f32.hip"]
+SOURCES = ["api.cpp", "fwd_bf16.hip", "fwd_f32.hip", "merge.hip", "bwd_bf16.hip", "bwd_dkdv.hip", "bwd_dq.hip",
+           "bwd_f32.hip"]
 ARCH = os.environ.get("BDLM_OFFLOAD_ARCH", "gfx950")
 # Per-source code-generation options.  The dK/dV kernel runs one wave per SIMD,
 # so its speed is its own instruction stream: the iterative ILP scheduler keeps
@@ -29,7 +29,12 @@ ARCH = os.environ.get("BDLM_OFFLOAD_ARCH", "gfx950")
 EXTRA_FLAGS = {"bwd_bf16.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp", "-mllvm", "-amdgpu-mfma-vgpr-form"],
                # score and dP accumulators in VGPRs (the softmax reads them); the
                # dK/dV accumulators are AGPR operands of inline-assembly MFMAs
-               "bwd_dkdv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+               "bwd_dkdv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+               # fp64 accumulators in VGPRs: in AGPRs the compiler copies them out and
+               # back around every loop iteration (36 instead of 71 TFLOP/s in a
+               # stand-alone stream of v_mfma_f64_16x16x4_f64)
+               "fwd_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+               "bwd_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def hipcc() -> str:

@@ -39,9 +39,9 @@ bdlm_status hip_fail(hipError_t e, const char* what) {
 }
 
 // ---- per-thread kernel timing (bdlm_timing_enable / bdlm_timing_collect)
-enum KernelId { kKFwdBf16 = 0, kKFwdF32, kKMerge, kKBwdPre, kKBwdBf16, kKBwdDq, kKBwdF32, kKCount };
-const char* const kKernelNames[kKCount] = {"fwd_bf16", "fwd_f32", "lse_merge", "bwd_pre", "bwd_dkdv_bf16",
-                                           "bwd_dq_bf16", "bwd_f32"};
+enum KernelId { kKFwdBf16 = 0, kKFwdF32, kKMerge, kKBwdDqF32, kKBwdBf16, kKBwdDq, kKBwdF32, kKBwdSum, kKCount };
+const char* const kKernelNames[kKCount] = {"fwd_bf16",    "fwd_f32",     "lse_merge",    "bwd_dq_f32",
+                                           "bwd_dkdv_bf16", "bwd_dq_bf16", "bwd_dkdv_f32", "bwd_dkdv_sum"};
 struct TimingRec {
   int id;
   hipEvent_t a, b;
@@ -78,6 +78,8 @@ hipError_t timed(int id, hipStream_t s, F&& f) {
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+
+size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 constexpr int64_t kMaxPos = (int64_t)1 << 30;
 
@@ -201,7 +203,90 @@ int bf16_query_rows(const bdlm_problem* p, int n_k, const bdlm_range* k_ranges, 
   return walk <= short_walk ? kQRowsShortBf16 : kQRowsLongBf16;
 }
 
-size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+// How the dK/dV walks of a backward are cut (SplitArgs).  A key tile's walk
+// covers the queries that see it: every query for the first clean keys, one
+// block for corrupted keys.  With few (batch, KV head, tile) workgroups the
+// longest walk, not the card, sets the kernel's time; cutting walks into
+// pieces of half the average load per CU (at least min_unit steps, below which
+// a workgroup's fixed cost and its partial sums outweigh the balance) brings
+// the kernel near the average.  Calls whose longest walk is below that
+// average are left whole.
+struct SplitPlan {
+  SplitArgs s;
+  size_t counts_bytes = 0, bytes = 0;  // of the workspace: counts, counts + partials
+};
+constexpr int kCus = 256;
+constexpr size_t kMaxSplitBytes = (size_t)256 << 20;
+constexpr int kMinUnitF32 = 8;
+
+// Calls whose dK/dV kernel takes chunks.
+bool can_split(const bdlm_problem* p, int, const bdlm_range*) { return p->dtype == BDLM_F32; }
+
+SplitPlan split_plan(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges, int n_k, const bdlm_range* k_ranges,
+                     bool enable) {
+  SplitPlan pl;
+  pl.s = SplitArgs{};
+  pl.s.unit = 1;
+  const bool f32 = p->dtype == BDLM_F32;
+  const int tile = f32 ? kRowsF32 : kBwdKeysBf16, step = f32 ? kRowsF32 : 32;
+  const int64_t pairs = (int64_t)p->kv_heads * p->batch, group = p->heads / p->kv_heads;
+  int64_t tiles = 0;
+  for (int j = 0; j < n_k; ++j) {
+    pl.s.chunks[j] = 1;
+    tiles += (k_ranges[j].len + tile - 1) / tile;
+  }
+  pl.s.wgs_per_pair = (int32_t)tiles;
+  // (enough workgroups: the average over them is what each CU gets anyway)
+  if (!enable || tiles * pairs > 16 * kCus) return pl;
+  // Walk lengths; a clean-context table (in device memory) may let every query see a clean key.
+  const MaskRule rule = host_rule(p, nullptr);
+  int64_t total = 0, longest = 0, walk[kMaxK] = {};
+  for (int j = 0; j < n_k; ++j) {
+    const bdlm_range& kr = k_ranges[j];
+    for (int64_t k0 = 0; k0 < kr.len; k0 += tile) {
+      const int first = (int)(kr.pos0 + k0), last = (int)(kr.pos0 + std::min<int64_t>(k0 + tile, kr.len) - 1);
+      int64_t n = 0;
+      for (int i = 0; i < n_q; ++i) {
+        const bdlm_range& qr = q_ranges[i];
+        int lo, hi, lo1, hi1;
+        query_interval(qr.stream, kr.stream, first, rule, lo, hi);
+        query_interval(qr.stream, kr.stream, last, rule, lo1, hi1);
+        if (p->clean_prefix && kr.stream == BDLM_CLEAN && qr.stream == BDLM_CORRUPTED) {
+          lo = 0;
+          hi1 = kBig;
+        }
+        const int64_t u0 = std::max<int64_t>(lo - qr.pos0, 0), u1 = std::min<int64_t>(hi1 - qr.pos0, qr.len);
+        if (u1 > u0) n += ((u1 + step - 1) / step - u0 / step) * group;
+      }
+      walk[j] = std::max(walk[j], n);
+      total += n * pairs;
+    }
+    longest = std::max(longest, walk[j]);
+  }
+  const int64_t average = total / kCus;
+  if (longest <= average) return pl;
+  for (int64_t unit = std::max<int64_t>(kMinUnitF32, average / 2);; unit *= 2) {
+    int64_t wgs = 0, slots = 0, chunked = 0;
+    for (int j = 0; j < n_k; ++j) {
+      const int64_t nt = (k_ranges[j].len + tile - 1) / tile;
+      const int64_t ch = std::max<int64_t>((walk[j] + unit - 1) / unit, 1);
+      pl.s.chunks[j] = (int32_t)ch;
+      wgs += nt * ch;
+      if (ch > 1) {
+        slots += nt * ch;
+        chunked += nt;
+      }
+    }
+    pl.s.unit = (int32_t)unit;
+    pl.s.wgs_per_pair = (int32_t)wgs;
+    pl.s.tiles_per_pair = (int32_t)chunked;
+    pl.s.slots_per_pair = (int32_t)slots;
+    const size_t slot = (size_t)2 * tile * p->head_dim * (f32 ? sizeof(double) : sizeof(float));
+    pl.counts_bytes = align256((size_t)(slots * pairs) * sizeof(int32_t));
+    pl.bytes = slots == 0 ? 0 : pl.counts_bytes + (size_t)(slots * pairs) * slot;
+    if (pl.bytes <= kMaxSplitBytes) return pl;
+  }
+}
 
 bdlm_status check_grid(int64_t tiles, int64_t mult) {
   if (tiles * mult >= ((int64_t)1 << 31))
@@ -248,7 +333,7 @@ bdlm_status bdlm_attn_fwd(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
     a.kr[j].k = k[j];
     a.kr[j].v = v[j];
   }
-  const int rows = p->dtype == BDLM_BF16 ? bf16_query_rows(p, n_k, k_ranges, kFwdShortWalk) : kFwdRowsF32;
+  const int rows = p->dtype == BDLM_BF16 ? bf16_query_rows(p, n_k, k_ranges, kFwdShortWalk) : kRowsF32;
   const int64_t tiles = tile_ranges(a.qr, n_q, rows);
   if ((st = check_grid(tiles, (int64_t)p->heads * p->batch)) != BDLM_OK) return st;
   a.total_tiles = (int32_t)tiles;
@@ -341,6 +426,17 @@ size_t bdlm_attn_bwd_workspace_bytes(const bdlm_problem* p, int32_t n_q, const b
     tot += 2 * align256(rows * p->heads * sizeof(float));  // LSE * log2(e), then D = rowsum(dO * O)
   }
   return tot;
+}
+
+size_t bdlm_attn_bwd_split_workspace_bytes(const bdlm_problem* p, int32_t n_q, const bdlm_range* q_ranges,
+                                           int32_t n_k, const bdlm_range* k_ranges) {
+  const size_t base = bdlm_attn_bwd_workspace_bytes(p, n_q, q_ranges);
+  if (check_problem(p) != BDLM_OK || check_counts(n_q, n_k, q_ranges, k_ranges) != BDLM_OK) return base;
+  for (int i = 0; i < n_q; ++i)
+    if (check_range(p, q_ranges[i], "query", i) != BDLM_OK) return base;
+  for (int j = 0; j < n_k; ++j)
+    if (check_range(p, k_ranges[j], "key", j) != BDLM_OK) return base;
+  return base + split_plan(p, n_q, q_ranges, n_k, k_ranges, can_split(p, n_q, q_ranges)).bytes;
 }
 
 }  // extern "C"
@@ -444,21 +540,23 @@ bdlm_status attn_bwd_impl(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
     a.kr[j].dk = dk[j];
     a.kr[j].dv = dv[j];
   }
-  const int keys = p->dtype == BDLM_BF16 ? kBwdKeysBf16 : kBwdKeysF32;
+  const int keys = p->dtype == BDLM_BF16 ? kBwdKeysBf16 : kRowsF32;
   const int64_t tiles = tile_ranges(a.kr, n_k, keys);
   if ((st = check_grid(tiles, (int64_t)p->kv_heads * p->batch)) != BDLM_OK) return st;
   a.total_tiles = (int32_t)tiles;
+  // Long walks are cut when the workspace has room for the partial sums behind the row statistics.
+  SplitPlan plan = split_plan(p, n_q, q_ranges, n_k, k_ranges, !use_scratch && can_split(p, n_q, q_ranges));
+  if (plan.bytes > 0 && workspace_bytes < need + plan.bytes) plan = split_plan(p, n_q, q_ranges, n_k, k_ranges, false);
+  a.split = plan.s;
   // The dQ kernel walks query tiles (of its own height).
   AttnArgs aq = a;
-  const int dq_rows = bf16_query_rows(p, n_k, k_ranges, kDqShortWalk);
-  if (p->dtype == BDLM_BF16) {
-    const int64_t qt = tile_ranges(aq.qr, n_q, dq_rows);
-    if ((st = check_grid(qt, (int64_t)p->heads * p->batch)) != BDLM_OK) return st;
-    aq.total_tiles = (int32_t)qt;
-    aq.interleave = 1;
-    for (int i = 1; i < n_q; ++i)
-      if (aq.qr[i].ntiles != aq.qr[0].ntiles) aq.interleave = 0;
-  }
+  const int dq_rows = p->dtype == BDLM_BF16 ? bf16_query_rows(p, n_k, k_ranges, kDqShortWalk) : kRowsF32;
+  const int64_t qt = tile_ranges(aq.qr, n_q, dq_rows);
+  if ((st = check_grid(qt, (int64_t)p->heads * p->batch)) != BDLM_OK) return st;
+  aq.total_tiles = (int32_t)qt;
+  aq.interleave = 1;
+  for (int i = 1; i < n_q; ++i)
+    if (aq.qr[i].ntiles != aq.qr[0].ntiles) aq.interleave = 0;
   // Validation done: place D and LSE*log2(e).
   char* base = static_cast<char*>(workspace);
   if (use_scratch && need > 0) {
@@ -472,6 +570,10 @@ bdlm_status attn_bwd_impl(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
     float* dl = need > 0 ? reinterpret_cast<float*>(base + ws_off[i] + arr) : nullptr;
     a.qr[i].l2 = aq.qr[i].l2 = l2;
     a.qr[i].delta = aq.qr[i].delta = dl;
+  }
+  if (plan.bytes > 0) {
+    a.split.counts = reinterpret_cast<int32_t*>(base + need);
+    a.split.partials = base + need + plan.counts_bytes;
   }
   // Visit key ranges heaviest first: clean ranges by ascending position (their
   // early keys are seen by the most queries), then corrupted ranges.
@@ -507,10 +609,15 @@ bdlm_status attn_bwd_impl(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
     });
     if (e != hipSuccess) return hip_fail(e, "backward dK/dV launch");
   } else {
-    e = timed(kKBwdPre, stream, [&] { return launch_bwd_pre(a, p->head_dim, stream); });
-    if (e != hipSuccess) return hip_fail(e, "backward pre-pass launch");
-    e = timed(kKBwdF32, stream, [&] { return launch_bwd_f32(a, p->head_dim, stream); });
-    if (e != hipSuccess) return hip_fail(e, "backward launch");
+    // The dQ kernel leaves D in the workspace for the dK/dV kernel.
+    e = timed(kKBwdDqF32, stream, [&] { return launch_bwd_dq_f32(aq, p->head_dim, stream); });
+    if (e != hipSuccess) return hip_fail(e, "backward dQ launch");
+    e = timed(kKBwdF32, stream, [&] { return launch_bwd_dkv_f32(a, p->head_dim, stream); });
+    if (e != hipSuccess) return hip_fail(e, "backward dK/dV launch");
+    if (plan.bytes > 0) {
+      e = timed(kKBwdSum, stream, [&] { return launch_bwd_sum_f32(a, p->head_dim, stream); });
+      if (e != hipSuccess) return hip_fail(e, "backward dK/dV sum launch");
+    }
   }
   return BDLM_OK;
 }

@@ -3,162 +3,404 @@
 // Exact gradients from the saved O and LSE (arXiv 2609.19242 App. C; the
 // query gradient eq:correctness-query-gradient and the key/value gradients
 // summed over every query row, eq:correctness-clean-gradient):
-//   P = exp(scale q.k - LSE),  dP = dO.v,  dS = P (dP - D),
+//   P = exp(scale q.k - LSE),  dP = dO.v,  dS = P (dP - D),  D = dO.O,
 //   dQ = scale sum_k dS k,  dK = scale sum_q dS q,  dV = sum_q P dO.
 // Inputs and outputs are fp32; scores, exponentials and sums are carried in
-// fp64.  Two deterministic passes walk the mask intervals of common.hpp directly:
-// one thread per query row for dQ, one thread per (key row, KV head) for dK
-// and dV (summing the query heads of its GQA group).  No atomics.
-#include "common.hpp"
+// fp64 on the fp64 matrix cores (f64tile.hpp).  Two deterministic passes, no
+// atomics:
+//  * dQ, query-major like the forward: a workgroup owns 16 query rows of one
+//    head (Q and dO as fp64 operands in LDS), its four waves share out the
+//    visible 16-key tiles; it also forms D and leaves it in the workspace.
+//  * dK/dV, key-major: a workgroup owns 16 keys of one KV head (K and V as
+//    fp64 operands in LDS), its four waves share out the visible (16-query
+//    tile, head of the group) units.  The early keys are seen by every query
+//    while late ones by few, so on small problems a few workgroups would run
+//    long after the rest; given workspace, long walks are cut into chunks of
+//    about equal work whose fp64 partial sums a second kernel adds up in
+//    chunk order.
+// Measured against one thread per query row (dQ) or key row (dK, dV), both
+// kernels together: L = 256, 2/2 heads, d 64: 10.7 ms -> 44 us; L = 1125, 8/2
+// heads, d 128: 621 -> 1.06 ms.
+#include "f64tile.hpp"
+#include "qtiles.hpp"
 
 namespace bdlm {
 
 namespace {
 
+constexpr int kWaves = 4;
+
 template <int D>
-__global__ __launch_bounds__(128) void bwd_dq_f32_kernel(const AttnArgs a) {
-  const int T = a.total_tiles;  // query tiles of kFwdRowsF32 rows
-  const int tile = blockIdx.x % T;
-  const int bh = blockIdx.x / T;
-  const int h = bh % a.heads, b = bh / a.heads;
-  int r = 0;
-  while (r + 1 < a.n_q && tile >= a.qr[r + 1].tile0) ++r;
-  const QRangeArg& qr = a.qr[r];
-  const int row = (tile - qr.tile0) * kFwdRowsF32 + (int)threadIdx.x;
-  if (row >= qr.len) return;
+__global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void bwd_dq_f32_kernel(
+    const AttnArgs a) {
+  constexpr int NC = D / 16, OPS = 16 * D;
+  // Q and dO as fp64 row operands during the walk, the waves' dQ^T sums after it
+  __shared__ __attribute__((aligned(16))) double lds[kWaves * 16 * kRedRow<D>];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i = lane & 15, g = lane >> 4;
+
+  const int n_wg = a.total_tiles * a.heads * a.batch, wg = workgroup_id();
+  if (wg >= n_wg) return;
+  const QTileItem it = q_tile_item(a, xcd_remap(wg, n_wg));
+  const QRangeArg& qr = a.qr[it.r];
+  const int kvh = it.h / a.group;
   const int64_t H = a.heads, HKV = a.kv_heads;
-  const int kvh = h / a.group;
-  const int64_t qoff = (((int64_t)b * qr.bstride + row) * H + h) * D;
-  const float* qp = (const float*)qr.q + qoff;
-  const float* dop = (const float*)qr.dO + qoff;
-  float qv[D], dov[D];
-  double dq[D];
+  const int row0 = it.t * 16, nvalid = imin(16, qr.len - row0);
+  const int64_t qoff = (((int64_t)it.b * qr.bstride + row0) * H + it.h) * D;
+  stage_row_operands<D>(lds, (const float*)qr.q + qoff, H * D, nvalid, tid, kWaves * 64);
+  stage_row_operands<D>(lds + OPS, (const float*)qr.dO + qoff, H * D, nvalid, tid, kWaves * 64);
+
+  // D = dO.O of this lane's query; the four lanes of a column share the row.
+  const int qi = imin(i, nvalid - 1);
+  double dl = 0.0;
+  {
+    const float* op = (const float*)qr.o + qoff + (int64_t)qi * H * D;
+    const float* dp = (const float*)qr.dO + qoff + (int64_t)qi * H * D;
 #pragma unroll
-  for (int d = 0; d < D; ++d) {
-    qv[d] = qp[d];
-    dov[d] = dop[d];
-    dq[d] = 0.0;
+    for (int c = 0; c < NC; ++c) {
+      const fl4 x = *(const fl4*)(op + 16 * c + 4 * g), y = *(const fl4*)(dp + 16 * c + 4 * g);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dl = __builtin_fma((double)x[e], (double)y[e], dl);
+    }
+    dl = col_sum(dl);
   }
-  const float lse = qr.lse[((int64_t)b * H + h) * qr.bstride + row];
-  const double Dq = (double)qr.delta[((int64_t)b * H + h) * qr.len + row];
-  const double scale = (double)a.scale;
-  const int pq = qr.pos0 + row;
-  if (lse != -INFINITY) {
-    for (int j = 0; j < a.n_k; ++j) {
-      const KRangeArg& kr = a.kr[j];
-      int lo, hi;
-      key_interval(qr.stream, pq, kr.stream, rule_of(a), lo, hi);
-      lo = imax(lo, kr.pos0);
-      hi = imin(hi, kr.pos0 + kr.len);
-      for (int kp = lo; kp < hi; ++kp) {
-        const int64_t off = (((int64_t)b * kr.bstride + (kp - kr.pos0)) * HKV + kvh) * D;
-        const float* kv = (const float*)kr.k + off;
-        const float* vv = (const float*)kr.v + off;
-        double s = 0.0, dp = 0.0;
+  const int64_t hrow = (int64_t)it.b * H + it.h;
+  const float lse = qr.lse[hrow * qr.bstride + row0 + qi];
+  if (w == 0 && g == 0 && i < nvalid) qr.delta[hrow * qr.len + row0 + i] = (float)dl;
+  const bool dead = lse == -INFINITY;  // the row sees no key
+  const double lse2 = (double)lse * kLog2eD;
+  const double c = (double)a.scale * kLog2eD;
+  const int pq = qr.pos0 + row0 + qi;
+  const int pq0 = qr.pos0 + row0, pq1 = qr.pos0 + row0 + nvalid - 1;
+  const bool any_dead = __builtin_amdgcn_ballot_w64(dead) != 0;
+  __syncthreads();
+
+  AccTiles<D> acc;
+  acc.zero();
+  int j = -1, t = 0, t1 = 0, f0 = 0, f1 = 0, skip = w;
+  auto advance = [&]() __attribute__((always_inline)) -> bool {
+    t += kWaves;
+    while (t >= t1) {
+      if (j >= 0) skip = t - t1;
+      if (++j >= a.n_k) return false;
+      key_tile_span(a, j, qr.stream, pq0, pq1, 16, t, t1, f0, f1);
+      t += skip;
+    }
+    return true;
+  };
+  t = t1 = -kWaves;
+  while (advance()) {
+    const KRangeArg& kr = a.kr[j];
+    const int64_t koff = (((int64_t)it.b * kr.bstride + t * 16) * HKV + kvh) * D;
+    const int krows = imin(16, kr.len - t * 16);
+    const RowTile kt = row_tile<D>(kr.k, koff, krows, HKV * D);
+    fl4 kx[NC], vx[NC];
+    ColOps<D> kc;
+    load_rows<D>(kx, kt, i, g);
+    load_rows<D>(vx, row_tile<D>(kr.v, koff, krows, HKV * D), i, g);
+    kc.load(kt, i, g);
+    const bool full = t >= f0 && t < f1 && !any_dead;
+    int lo = 0, wid = 0;
+    if (!full) lane_key_interval(a, j, qr.stream, pq, lo, wid);
+    if (dead) wid = 0;
+    const int kbase = kr.pos0 + t * 16 - lo;
+    auto seen = [&](int row) { return full || (unsigned)(kbase + row) < (unsigned)wid; };
+
+    const f64x4 s = row_product<D>(kx, lds, lane);
+    const f64x4 dp = row_product<D>(vx, lds + OPS, lane);
+    f64x4 ds;
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-          s = fma((double)qv[d], (double)kv[d], s);
-          dp = fma((double)dov[d], (double)vv[d], dp);
-        }
-        const double p = exp(s * scale - (double)lse);
-        const double ds = p * (dp - Dq);
+    for (int r = 0; r < 4; ++r) {
+      const bool see = seen(4 * r + g);
+      const double p = exp2_f64(see ? __builtin_fma(s[r], c, -lse2) : kHidden);
+      ds[r] = p * (see ? dp[r] - dl : 0.0);
+    }
+    // as in the forward: hidden keys must not spread an infinity or NaN of K
+    if (full || !kc.non_finite()) col_product<D>(acc, kc, ds);
+    else col_product_guarded<D>(acc, kt, ds, seen, i, g);
+  }
+
+  __syncthreads();  // every wave has left the walk: Q and dO are no longer read
+  acc_to_lds<D>(acc, lds + w * 16 * kRedRow<D>, i, g);
+  __syncthreads();
+  constexpr int EPT = 16 * D / (kWaves * 64);
+  const int q = tid / (D / EPT), d0 = (tid % (D / EPT)) * EPT;
+  if (q < nvalid) {
+    float* out = (float*)qr.dq + qoff + (int64_t)q * H * D + d0;
 #pragma unroll
-        for (int d = 0; d < D; ++d) dq[d] = fma(ds, (double)kv[d], dq[d]);
+    for (int e4 = 0; e4 < EPT / 4; ++e4) {
+      fl4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        double x = 0.0;
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) x += lds[(k * 16 + q) * kRedRow<D> + d0 + 4 * e4 + e];
+        o[e] = (float)(x * (double)a.scale);
       }
+      *(fl4*)(out + 4 * e4) = o;
     }
   }
-  float* out = (float*)qr.dq + qoff;
-#pragma unroll
-  for (int d = 0; d < D; ++d) out[d] = (float)(dq[d] * scale);
+}
+
+// The key tile of a workgroup of the dK/dV kernel: tiles of a (batch, KV head)
+// pair in visiting order (heaviest range first), a tile's chunks one after the
+// other.
+struct KeyTileItem {
+  int b, kvh, r, t, chunk;
+  int64_t slot;  // index of the tile's chunk 0 in the partials (chunked ranges)
+};
+__device__ inline KeyTileItem key_tile_item(const AttnArgs& a, int logical) {
+  const int per = a.split.wgs_per_pair;
+  KeyTileItem it;
+  const int bk = logical / per;
+  int rank = logical - bk * per;
+  it.b = bk / a.kv_heads;
+  it.kvh = bk - it.b * a.kv_heads;
+  it.r = a.order[0];
+  int64_t base = 0;
+  for (int n = 0; n < a.n_k; ++n) {
+    const int r = a.order[n], ch = a.split.chunks[r], nw = a.kr[r].ntiles * ch;
+    it.r = r;
+    if (rank < nw) break;
+    rank -= nw;
+    if (ch > 1) base += nw;
+  }
+  const int ch = a.split.chunks[it.r];
+  it.t = rank / ch;
+  it.chunk = rank - it.t * ch;
+  it.slot = (int64_t)bk * a.split.slots_per_pair + base + (int64_t)it.t * ch;
+  return it;
 }
 
 template <int D>
-__global__ __launch_bounds__(128) void bwd_dkv_f32_kernel(const AttnArgs a) {
-  const int T = a.total_tiles;  // key tiles of kBwdKeysF32 rows
-  const int tile = blockIdx.x % T;
-  const int bk = blockIdx.x / T;
-  const int kvh = bk % a.kv_heads, b = bk / a.kv_heads;
-  int r = 0;
-  while (r + 1 < a.n_k && tile >= a.kr[r + 1].tile0) ++r;
-  const KRangeArg& kr = a.kr[r];
-  const int row = (tile - kr.tile0) * kBwdKeysF32 + (int)threadIdx.x;
-  if (row >= kr.len) return;
+__global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void bwd_dkv_f32_kernel(
+    const AttnArgs a) {
+  constexpr int NC = D / 16, OPS = 16 * D;
+  // K and V as fp64 row operands during the walk, the waves' sums after it
+  __shared__ __attribute__((aligned(16))) double lds[kWaves * 16 * kRedRow<D>];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i = lane & 15, g = lane >> 4;
+  const int n_wg = a.split.wgs_per_pair * a.kv_heads * a.batch, wg = workgroup_id();
+  if (wg >= n_wg) return;
+  const KeyTileItem it = key_tile_item(a, xcd_remap(wg, n_wg));
+  const KRangeArg& kr = a.kr[it.r];
   const int64_t H = a.heads, HKV = a.kv_heads;
-  const int64_t koff = (((int64_t)b * kr.bstride + row) * HKV + kvh) * D;
-  const float* kp_ = (const float*)kr.k + koff;
-  const float* vp_ = (const float*)kr.v + koff;
-  float kv[D], vv[D];
-  double dk[D], dv[D];
-#pragma unroll
-  for (int d = 0; d < D; ++d) {
-    kv[d] = kp_[d];
-    vv[d] = vp_[d];
-    dk[d] = 0.0;
-    dv[d] = 0.0;
+  const int row0 = it.t * 16, nvalid = imin(16, kr.len - row0);
+  const int ki = imin(i, nvalid - 1), pk = kr.pos0 + row0 + ki;
+
+  // Units of the walk: (query range, 16-query tile, head of the group).
+  const int kp0 = kr.pos0 + row0, kp1 = kr.pos0 + row0 + nvalid - 1;
+  struct Span {
+    int t0, t1, f0, f1;
+  };
+  auto span = [&](int q) __attribute__((always_inline)) -> Span {
+    const QRangeArg& qr = a.qr[q];
+    int lo0, hi0, lo1, hi1;
+    query_interval(qr.stream, kr.stream, kp0, rule_of(a), lo0, hi0);
+    query_interval(qr.stream, kr.stream, kp1, rule_of(a), lo1, hi1);
+    const int u0 = imax(lo0 - qr.pos0, 0), u1 = imin(hi1 - qr.pos0, qr.len);
+    Span s{0, 0, 0, 0};
+    if (u1 > u0) {
+      s.t0 = u0 / 16;
+      s.t1 = (u1 + 15) / 16;
+      const int i0 = imax(lo1 - qr.pos0, 0), i1 = imin(hi0 - qr.pos0, qr.len);
+      if (i1 > i0) {
+        s.f0 = (i0 + 15) / 16;
+        s.f1 = i1 / 16;
+      }
+    }
+    return s;
+  };
+  int units = 0;
+  for (int q = 0; q < a.n_q; ++q) {
+    const Span s = span(q);
+    units += (s.t1 - s.t0) * a.group;
   }
-  const double scale = (double)a.scale;
-  const int pk = kr.pos0 + row;
-  for (int hq = 0; hq < a.group; ++hq) {
-    const int h = kvh * a.group + hq;
-    for (int i = 0; i < a.n_q; ++i) {
-      const QRangeArg& qr = a.qr[i];
+  const int nch = a.split.chunks[it.r] > 1 ? chunks_of(units, a.split.unit, a.split.chunks[it.r]) : 1;
+  if (it.chunk == 0 && tid == 0 && a.split.chunks[it.r] > 1) a.split.counts[it.slot] = nch;
+  if (it.chunk >= nch) return;
+  const int n0 = (int)((int64_t)units * it.chunk / nch), n1 = (int)((int64_t)units * (it.chunk + 1) / nch);
+
+  const int64_t koff = (((int64_t)it.b * kr.bstride + row0) * HKV + it.kvh) * D;
+  stage_row_operands<D>(lds, (const float*)kr.k + koff, HKV * D, nvalid, tid, kWaves * 64);
+  stage_row_operands<D>(lds + OPS, (const float*)kr.v + koff, HKV * D, nvalid, tid, kWaves * 64);
+  __syncthreads();
+
+  const double c = (double)a.scale * kLog2eD;
+  AccTiles<D> dk, dv;
+  dk.zero();
+  dv.zero();
+  int q = -1, q_first = 0, q_end = 0;  // the current range's units [q_first, q_end)
+  Span sp{0, 0, 0, 0};
+  int qa = 0, qw = 0;  // the queries of the range that see this lane's key
+  for (int n = n0 + w; n < n1; n += kWaves) {
+    while (n >= q_end) {
+      sp = span(++q);
+      q_first = q_end;
+      q_end += (sp.t1 - sp.t0) * a.group;
+      const QRangeArg& qr = a.qr[q];
       int lo, hi;
       query_interval(qr.stream, kr.stream, pk, rule_of(a), lo, hi);
-      lo = imax(lo, qr.pos0);
-      hi = imin(hi, qr.pos0 + qr.len);
-      for (int pq = lo; pq < hi; ++pq) {
-        const int qrow = pq - qr.pos0;
-        const float lse = qr.lse[((int64_t)b * H + h) * qr.bstride + qrow];
-        if (lse == -INFINITY) continue;
-        const int64_t qoff = (((int64_t)b * qr.bstride + qrow) * H + h) * D;
-        const float* qv = (const float*)qr.q + qoff;
-        const float* dov = (const float*)qr.dO + qoff;
-        double s = 0.0, dp = 0.0;
+      qa = imax(lo, qr.pos0);
+      qw = imax(imin(hi, qr.pos0 + qr.len) - qa, 0);
+    }
+    const QRangeArg& qr = a.qr[q];
+    const int tt = (n - q_first) / a.group, t = sp.t0 + tt;
+    const int h = it.kvh * a.group + (n - q_first) - tt * a.group;
+    const int64_t hrow = (int64_t)it.b * H + h;
+    const int64_t qoff = (((int64_t)it.b * qr.bstride + t * 16) * H + h) * D;
+    const int qrows = imin(16, qr.len - t * 16);
+    const RowTile qt = row_tile<D>(qr.q, qoff, qrows, H * D), ot = row_tile<D>(qr.dO, qoff, qrows, H * D);
+    fl4 qx[NC], ox[NC];
+    ColOps<D> cx;
+    load_rows<D>(qx, qt, i, g);
+    load_rows<D>(ox, ot, i, g);
+    float lse[4], dl[4];
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-          s = fma((double)qv[d], (double)kv[d], s);
-          dp = fma((double)dov[d], (double)vv[d], dp);
-        }
-        const double p = exp(s * scale - (double)lse);
-        const double ds = p * (dp - (double)qr.delta[((int64_t)b * H + h) * qr.len + qrow]);
+    for (int r = 0; r < 4; ++r) {
+      const int row = imin(t * 16 + 4 * r + g, qr.len - 1);
+      lse[r] = qr.lse[hrow * qr.bstride + row];
+      dl[r] = qr.delta[hrow * qr.len + row];
+    }
+    const f64x4 s = row_product<D>(qx, lds, lane);
+    cx.load(ot, i, g);
+    const f64x4 dp = row_product<D>(ox, lds + OPS, lane);
+    bool dead = false;
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-          dv[d] = fma(p, (double)dov[d], dv[d]);
-          dk[d] = fma(ds, (double)qv[d], dk[d]);
-        }
+    for (int r = 0; r < 4; ++r) dead |= lse[r] == -INFINITY;
+    const bool full = t >= sp.f0 && t < sp.f1 && __builtin_amdgcn_ballot_w64(dead) == 0;
+    const int qbase = qr.pos0 + t * 16 - qa;
+    auto seen_row = [&](int row) { return full || (unsigned)(qbase + row) < (unsigned)qw; };
+    f64x4 p, ds;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bool see = seen_row(4 * r + g) && lse[r] != -INFINITY;
+      p[r] = exp2_f64(see ? __builtin_fma(s[r], c, -(double)lse[r] * kLog2eD) : kHidden);
+      ds[r] = p[r] * (see ? dp[r] - (double)dl[r] : 0.0);
+    }
+    // guarded form: a row that sees no key hides from every column
+    auto seen = [&](int row) {
+      const float z = qr.lse[hrow * qr.bstride + imin(t * 16 + row, qr.len - 1)];
+      return seen_row(row) && z != -INFINITY;
+    };
+    if (full || !cx.non_finite()) {
+      col_product<D>(dv, cx, p);
+    } else {
+          col_product_guarded<D>(dv, ot, p, seen, i, g);
+    }
+    cx.load(qt, i, g);
+    if (full || !cx.non_finite()) {
+      col_product<D>(dk, cx, ds);
+    } else {
+          col_product_guarded<D>(dk, qt, ds, seen, i, g);
+    }
+  }
+
+  // Sum the waves through LDS, dV then dK; one chunk writes the gradients,
+  // several write fp64 partials [slot][dV, dK][key][d].
+  constexpr int EPT = 16 * D / (kWaves * 64);
+  const int k = tid / (D / EPT), d0 = (tid % (D / EPT)) * EPT;
+#pragma unroll
+  for (int which = 0; which < 2; ++which) {
+    __syncthreads();
+    acc_to_lds<D>(which == 0 ? dv : dk, lds + w * 16 * kRedRow<D>, i, g);
+    __syncthreads();
+    double x[EPT];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      x[e] = 0.0;
+#pragma unroll
+      for (int u = 0; u < kWaves; ++u) x[e] += lds[(u * 16 + k) * kRedRow<D> + d0 + e];
+    }
+    if (nch > 1) {
+      double* dst = (double*)a.split.partials + ((it.slot + it.chunk) * 2 + which) * OPS + k * D + d0;
+#pragma unroll
+      for (int e = 0; e < EPT; e += 2) *(f64x2*)(dst + e) = f64x2{x[e], x[e + 1]};
+    } else if (k < nvalid) {
+      float* dst = (float*)(which == 0 ? kr.dv : kr.dk) + koff + (int64_t)k * HKV * D + d0;
+      const double sc = which == 0 ? 1.0 : (double)a.scale;
+#pragma unroll
+      for (int e4 = 0; e4 < EPT / 4; ++e4) {
+        fl4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (float)(x[4 * e4 + e] * sc);
+        *(fl4*)(dst + 4 * e4) = o;
       }
     }
   }
-  float* dkp = (float*)kr.dk + koff;
-  float* dvp = (float*)kr.dv + koff;
+}
+
+// dK, dV of the chunked key tiles: the sum of the chunks' partials in chunk
+// order.  One workgroup per tile (grid: every tile of the chunked ranges).
+template <int D>
+__global__ __launch_bounds__(256) void bwd_sum_f32_kernel(const AttnArgs a) {
+  constexpr int OPS = 16 * D, EPT = OPS / 256;
+  int tile = blockIdx.x % a.split.tiles_per_pair;
+  const int bk = blockIdx.x / a.split.tiles_per_pair;
+  const int b = bk / a.kv_heads, kvh = bk - b * a.kv_heads;
+  int r = a.order[0];
+  int64_t slot = (int64_t)bk * a.split.slots_per_pair;
+  for (int n = 0; n < a.n_k; ++n) {
+    r = a.order[n];
+    const int ch = a.split.chunks[r];
+    if (ch <= 1) continue;
+    if (tile < a.kr[r].ntiles) break;
+    tile -= a.kr[r].ntiles;
+    slot += (int64_t)a.kr[r].ntiles * ch;
+  }
+  const KRangeArg& kr = a.kr[r];
+  slot += (int64_t)tile * a.split.chunks[r];
+  const int nch = a.split.counts[slot];
+  if (nch <= 1) return;
+  const int nvalid = imin(16, kr.len - tile * 16);
+  const int k = threadIdx.x / (D / EPT), d0 = (threadIdx.x % (D / EPT)) * EPT;
+  if (k >= nvalid) return;
+  const int64_t off = (((int64_t)b * kr.bstride + tile * 16 + k) * a.kv_heads + kvh) * D + d0;
 #pragma unroll
-  for (int d = 0; d < D; ++d) {
-    dkp[d] = (float)(dk[d] * scale);
-    dvp[d] = (float)dv[d];
+  for (int which = 0; which < 2; ++which) {
+    double x[EPT] = {};
+    for (int ch = 0; ch < nch; ++ch) {
+      const double* src = (const double*)a.split.partials + ((slot + ch) * 2 + which) * OPS + k * D + d0;
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) x[e] += src[e];
+    }
+    float* dst = (float*)(which == 0 ? kr.dv : kr.dk) + off;
+    const double sc = which == 0 ? 1.0 : (double)a.scale;
+#pragma unroll
+    for (int e4 = 0; e4 < EPT / 4; ++e4) {
+      fl4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = (float)(x[4 * e4 + e] * sc);
+      *(fl4*)(dst + 4 * e4) = o;
+    }
   }
 }
 
 }  // namespace
 
-// a.total_tiles holds the key-tile count; the query-tile count is recomputed here.
-hipError_t launch_bwd_f32(const AttnArgs& a, int head_dim, hipStream_t s) {
-  AttnArgs aq = a;
-  int tq = 0;
-  for (int i = 0; i < a.n_q; ++i) {
-    aq.qr[i].tile0 = tq;
-    tq += (a.qr[i].len + kFwdRowsF32 - 1) / kFwdRowsF32;
-  }
-  aq.total_tiles = tq;
-  const int nq = tq * a.heads * a.batch;
-  const int nk = a.total_tiles * a.kv_heads * a.batch;
-  if (nq > 0) {
-    if (head_dim == 128) hipLaunchKernelGGL((bwd_dq_f32_kernel<128>), dim3(nq), dim3(128), 0, s, aq);
-    else hipLaunchKernelGGL((bwd_dq_f32_kernel<64>), dim3(nq), dim3(128), 0, s, aq);
-  }
-  if (nk > 0) {
-    if (head_dim == 128) hipLaunchKernelGGL((bwd_dkv_f32_kernel<128>), dim3(nk), dim3(128), 0, s, a);
-    else hipLaunchKernelGGL((bwd_dkv_f32_kernel<64>), dim3(nk), dim3(128), 0, s, a);
-  }
+// a.total_tiles and a.qr's tiles describe 16-row query tiles.
+hipError_t launch_bwd_dq_f32(const AttnArgs& a, int head_dim, hipStream_t s) {
+  const int n = a.total_tiles * a.heads * a.batch;
+  if (n == 0) return hipSuccess;
+  if (head_dim == 128) hipLaunchKernelGGL((bwd_dq_f32_kernel<128>), grid_of(n), dim3(kWaves * 64), 0, s, a);
+  else hipLaunchKernelGGL((bwd_dq_f32_kernel<64>), grid_of(n), dim3(kWaves * 64), 0, s, a);
+  return hipGetLastError();
+}
+
+// a.kr's tiles describe 16-row key tiles; a.split is filled.
+hipError_t launch_bwd_dkv_f32(const AttnArgs& a, int head_dim, hipStream_t s) {
+  const int n = a.split.wgs_per_pair * a.kv_heads * a.batch;
+  if (n == 0) return hipSuccess;
+  if (head_dim == 128) hipLaunchKernelGGL((bwd_dkv_f32_kernel<128>), grid_of(n), dim3(kWaves * 64), 0, s, a);
+  else hipLaunchKernelGGL((bwd_dkv_f32_kernel<64>), grid_of(n), dim3(kWaves * 64), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_bwd_sum_f32(const AttnArgs& a, int head_dim, hipStream_t s) {
+  const int n = a.split.tiles_per_pair * a.kv_heads * a.batch;
+  if (n == 0) return hipSuccess;
+  if (head_dim == 128) hipLaunchKernelGGL((bwd_sum_f32_kernel<128>), dim3(n), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((bwd_sum_f32_kernel<64>), dim3(n), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -145,6 +145,26 @@ struct KRangeArg {
   void* dv;
 };
 
+// Long dK/dV walks cut into chunks (split_plan in api.cpp): key range r's
+// tiles are walked by up to chunks[r] workgroups, ceil(walk / unit) of them at
+// work, each of which leaves its partial sums in a slot of `partials`; a
+// second kernel adds them up in chunk order.  chunks[r] = 1: one workgroup per
+// tile, which writes the gradients itself.
+struct SplitArgs {
+  int32_t wgs_per_pair;    // workgroups per (batch, KV head): sum over ranges of tiles x chunks
+  int32_t tiles_per_pair;  // tiles of the chunked ranges per (batch, KV head)
+  int32_t unit;            // walk steps per chunk aimed at
+  int32_t slots_per_pair;  // partial slots per (batch, KV head)
+  int32_t* counts;         // chunks at work, at the slot of a tile's chunk 0
+  void* partials;
+  int32_t chunks[kMaxK];
+};
+
+// Workgroups that share a walk of n steps: about `unit` steps each, at most max_chunks.
+__host__ __device__ inline int chunks_of(int n, int unit, int max_chunks) {
+  return imin(imax((n + unit - 1) / unit, 1), max_chunks);
+}
+
 struct AttnArgs {
   int32_t n_q, n_k;
   int32_t batch, heads, kv_heads, group;
@@ -164,6 +184,7 @@ struct AttnArgs {
   int32_t order[kMaxK];  // bwd: visiting order of key ranges (heaviest first)
   QRangeArg qr[kMaxQ];
   KRangeArg kr[kMaxK];
+  SplitArgs split;       // dK/dV kernels
 };
 
 struct MergeArgs {
@@ -216,11 +237,12 @@ __device__ inline void pair_and_rank(int logical, int T, int nbk, int& bk, int& 
 hipError_t launch_fwd_bf16(const AttnArgs& a, int head_dim, int rows, hipStream_t s);
 hipError_t launch_fwd_f32(const AttnArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_merge(const MergeArgs& a, int head_dim, int part_dtype, int out_dtype, hipStream_t s);
-hipError_t launch_bwd_pre(const AttnArgs& a, int head_dim, hipStream_t s);  // fp32 path
 hipError_t launch_bwd_bf16(const AttnArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_bwd_dkdv(const AttnArgs& a, hipStream_t s);
 hipError_t launch_bwd_dq_bf16(const AttnArgs& a, int head_dim, int rows, hipStream_t s);
-hipError_t launch_bwd_f32(const AttnArgs& a, int head_dim, hipStream_t s);
+hipError_t launch_bwd_dq_f32(const AttnArgs& a, int head_dim, hipStream_t s);
+hipError_t launch_bwd_dkv_f32(const AttnArgs& a, int head_dim, hipStream_t s);
+hipError_t launch_bwd_sum_f32(const AttnArgs& a, int head_dim, hipStream_t s);
 
 // The walk of a key tile of the scheduled dK/dV kernel over its visible query
 // rows, by step index.  The rows come as up to two query ranges; range r is
@@ -308,8 +330,7 @@ constexpr int kQRowsLongBf16 = 256;
 constexpr int kQRowsShortBf16 = 128;
 constexpr int64_t kFwdShortWalk = 16384;  // keys a row may see for the 128-row forward
 constexpr int64_t kDqShortWalk = 8192;    // ... and for the 128-row dQ kernel
-constexpr int kFwdRowsF32 = 128;
+constexpr int kRowsF32 = 16;       // fp32 path: query rows, or key rows, per workgroup
 constexpr int kBwdKeysBf16 = 128;  // key rows per backward workgroup (4 waves x 32)
-constexpr int kBwdKeysF32 = 128;
 
 }  // namespace bdlm
