@@ -289,7 +289,7 @@ SplitPlan split_plan(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges,
 }
 
 bdlm_status check_grid(int64_t tiles, int64_t mult) {
-  if (tiles * mult >= ((int64_t)1 << 31))
+  if (tiles * mult >= ((int64_t)1 << 31) - 8)  // (launches round up to a multiple of 8)
     return fail(BDLM_ERR_UNSUPPORTED, "problem needs %lld workgroups (limit 2^31)", (long long)(tiles * mult));
   return BDLM_OK;
 }

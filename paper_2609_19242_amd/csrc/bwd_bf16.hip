@@ -76,9 +76,8 @@ __global__ __launch_bounds__(256) void bwd_bf16_kernel(const AttnArgs a) {
 
   // ---- work item: (batch, KV head, key range, key tile); heaviest tiles first per XCD
   const int T = a.total_tiles;
-  const int logical = xcd_remap(blockIdx.x, T * a.kv_heads * a.batch);
   int bk, order;
-  pair_and_rank(logical, T, a.kv_heads * a.batch, bk, order);
+  if (!xcd_pair_item(blockIdx.x, a.kv_heads * a.batch, T, true, bk, order)) return;
   const int b = bk / a.kv_heads, kvh = bk - (bk / a.kv_heads) * a.kv_heads;
   int r = a.order[0], t = order;
   for (int n = 0; n < a.n_k; ++n) {
@@ -600,7 +599,7 @@ void launch_hm(const AttnArgs& a, int n, hipStream_t s) {
 }
 
 hipError_t launch_bwd_bf16(const AttnArgs& a, int head_dim, hipStream_t s) {
-  const int n = a.total_tiles * a.kv_heads * a.batch;
+  const int n = workgroups_for(a.total_tiles * a.kv_heads * a.batch);
   if (n == 0) return hipSuccess;
   if (head_dim == 128) launch_hm<128>(a, n, s);
   else launch_hm<64>(a, n, s);

@@ -40,8 +40,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int l32 = lane & 31, half = lane >> 5;
   const int G = lane >> 4, sl = lane & 15;
 
-  const int n_wg = a.total_tiles * a.heads * a.batch;
-  const QTileItem it = q_tile_item(a, xcd_remap(blockIdx.x, n_wg));
+  QTileItem it;
+  if (!q_tile_item(a, blockIdx.x, it)) return;
   const QRangeArg& qr = a.qr[it.r];
   const int kvh = it.h / a.group;
   const int row0 = it.t * BM;
@@ -395,7 +395,7 @@ void launch_rows(const AttnArgs& a, int rows, int n, hipStream_t s) {
 
 // a.total_tiles / qr[i].tile0 / ntiles must describe query tiles of `rows` rows.
 hipError_t launch_bwd_dq_bf16(const AttnArgs& a, int head_dim, int rows, hipStream_t s) {
-  const int n = a.total_tiles * a.heads * a.batch;
+  const int n = workgroups_for(a.total_tiles * a.heads * a.batch);
   if (n == 0) return hipSuccess;
   if (head_dim == 128) launch_rows<128>(a, rows, n, s);
   else launch_rows<64>(a, rows, n, s);

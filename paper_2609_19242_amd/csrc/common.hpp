@@ -203,35 +203,40 @@ __host__ __device__ inline MaskRule rule_of(const AttnArgs& a) {
   return MaskRule{a.M, a.intra, a.window, a.nblk, a.L, a.prefix};
 }
 
-// Blocks are dispatched round-robin over the 8 XCDs of an MI355X.  Remap the
-// hardware block id so that consecutive logical ids run on the same XCD (and
-// share its L2): XCD x gets the logical span [x*n/8, (x+1)*n/8).
-__device__ inline int xcd_remap(int wg, int n) {
-  const int q = n >> 3, r = n & 7;
-  const int xcd = wg & 7, slot = wg >> 3;
-  return (xcd < r) ? xcd * (q + 1) + slot : r * (q + 1) + (xcd - r) * q + slot;
-}
-
-// Logical work id (after xcd_remap) -> (pair, rank) for the key-major dK/dV
-// kernels: T key tiles per (batch, KV head) pair, nbk pairs, the tiles of a
-// pair numbered heaviest first.  When the pairs divide evenly over the 8 XCDs,
-// the m pairs of one XCD are interleaved tile by tile, so that the heaviest
-// tiles of all of them start first on the XCD's CUs (one pair after the other
-// left the second pair's heaviest tiles to start late and end last: 7-8% of
-// the kernel at batch 2 and 4, 4K keys).  Otherwise pairs follow one another.
-// (The query-major kernels keep pairs in sequence: there interleaving puts the
-// K/V of several heads in one XCD's L2 at once and was slower.)
-__device__ inline void pair_and_rank(int logical, int T, int nbk, int& bk, int& rank) {
-  if (nbk > 8 && nbk % 8 == 0) {
-    const int m = nbk >> 3, span = m * T;
-    const int x = logical / span, local = logical - x * span;
-    rank = local / m;
-    bk = x * m + (local - rank * m);
+// Workgroups are dispatched round-robin over the 8 XCDs of an MI355X, each
+// with its own L2.  Work item of hardware workgroup wg when every one of nbk
+// (batch, KV head) pairs has T items, numbered heaviest first: the XCDs form
+// g = gcd(nbk, 8) groups of 8 / g, each serving nbk / g pairs, and a group's
+// items are dealt to its XCDs in turn, so that a pair's K/V (or Q/dO) meets in
+// as few L2s as the balance allows and every XCD gets its share of heavy and
+// light items.  (Contiguous spans of items per XCD, right for nbk a multiple
+// of 8, gave one XCD all the heavy items of a pair and another all the light
+// ones otherwise: at 8K, 4 KV heads, the heavy half of a causal triangle is
+// three quarters of the work.)  The launch has workgroups_for() workgroups;
+// false: this one has no item.
+// interleave: a group's pairs advance side by side instead of one after the
+// other.  The key-major kernels do, so that the heaviest tiles of all pairs
+// start first (one pair after the other left the second pair's heaviest tiles
+// to start late and end last: 7-8% of the kernel at batch 2 and 4, 4K keys);
+// the query-major ones keep pairs in sequence (side by side they put the K/V
+// of several heads in one XCD's L2 at once and were slower).
+__host__ __device__ inline bool xcd_pair_item(int wg, int nbk, int T, bool interleave, int& pair, int& rank) {
+  const int lg = (nbk & 7) == 0 ? 3 : (nbk & 3) == 0 ? 2 : (nbk & 1) == 0 ? 1 : 0;  // log2 g
+  const int lm = 3 - lg, xcd = wg & 7;
+  const int grp = xcd >> lm, m = nbk >> lg;
+  const int item = ((wg >> 3) << lm) + (xcd & ((1 << lm) - 1));
+  if (item >= m * T) return false;
+  if (interleave) {
+    rank = item / m;
+    pair = grp * m + item - rank * m;
   } else {
-    bk = logical / T;
-    rank = logical - bk * T;
+    pair = item / T;
+    rank = item - pair * T;
+    pair += grp * m;
   }
+  return true;
 }
+inline int workgroups_for(int items) { return (items + 7) & ~7; }
 
 // Launchers (defined in the .hip files).  All return hipSuccess or the launch error.
 hipError_t launch_fwd_bf16(const AttnArgs& a, int head_dim, int rows, hipStream_t s);

