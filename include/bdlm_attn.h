@@ -80,7 +80,7 @@ typedef enum {
   BDLM_ERR_INVALID = -1,     /* malformed argument: sizes, ranges, null or misaligned pointers */
   BDLM_ERR_UNSUPPORTED = -2, /* well-formed but not implemented: head_dim, dtype, too many ranges */
   BDLM_ERR_HIP = -3,         /* a HIP call or kernel launch failed */
-  BDLM_ERR_WORKSPACE = -4    /* workspace missing or smaller than bdlm_attn_bwd_workspace_bytes */
+  BDLM_ERR_WORKSPACE = -4    /* workspace missing or too small for the row statistics */
 } bdlm_status;
 
 typedef enum { BDLM_BF16 = 0, BDLM_F32 = 1 } bdlm_dtype;
@@ -211,21 +211,16 @@ bdlm_status bdlm_lse_merge_strided(int64_t batch, int64_t rows, int32_t heads, i
                                    int32_t out_dtype, int64_t out_batch_stride,
                                    hipStream_t stream);
 
-/* Workspace bytes bdlm_attn_bwd needs for these query ranges: per range two
+/* Workspace bytes bdlm_attn_bwd takes for these query ranges: per range two
  * fp32 arrays of batch * len * heads values (each rounded up to 256 bytes),
- * LSE * log2(e) and the row dots D = rowsum(dO * O).  Ranges whose
- * batch * len * heads exceeds 2^28 are rejected by bdlm_attn_bwd. */
+ * LSE * log2(e) and the row dots D = rowsum(dO * O), which every call needs;
+ * and, for problems with too few key tiles to fill the card, up to 256 MiB for
+ * the partial sums of dK/dV walks that are cut into chunks and run side by
+ * side.  bdlm_attn_bwd takes any size from the arrays' up; with less than this
+ * function's (or with more key rows than both streams hold) it leaves the
+ * walks whole: the same sums in another order, slower.  Ranges whose batch *
+ * len * heads exceeds 2^28 are rejected by bdlm_attn_bwd. */
 size_t bdlm_attn_bwd_workspace_bytes(const bdlm_problem* p, int32_t n_q, const bdlm_range* q_ranges);
-
-/* Workspace bytes with which bdlm_attn_bwd may also cut long dK/dV walks into
- * chunks that run side by side (for calls with too few key tiles to fill the
- * card): bdlm_attn_bwd_workspace_bytes() plus room for the chunks' partial
- * sums, at most 256 MiB more; equal to it where cutting does not help.  The
- * call takes either size.  The sums of a cut walk are added in a fixed order
- * (results are reproducible), which is another order than in an uncut walk:
- * dK and dV may differ from the smaller workspace's in the last bits. */
-size_t bdlm_attn_bwd_split_workspace_bytes(const bdlm_problem* p, int32_t n_q, const bdlm_range* q_ranges,
-                                           int32_t n_k, const bdlm_range* k_ranges);
 
 /*
  * Backward from the saved (final, merged) O and LSE (App. C fused backward;
@@ -235,8 +230,8 @@ size_t bdlm_attn_bwd_split_workspace_bytes(const bdlm_problem* p, int32_t n_q, c
  * summed over every query row of every query range, and over the query heads
  * of each KV head.  dq[i] like q[i]; dk[j], dv[j] like k[j]; all overwritten.
  * Key rows no query sees get dK = dV = 0.
- * workspace: device memory of at least bdlm_attn_bwd_workspace_bytes(), 256-byte
- * aligned, contents ignored on entry.
+ * workspace: device memory of bdlm_attn_bwd_workspace_bytes() (see there),
+ * 256-byte aligned, contents ignored on entry.
  */
 bdlm_status bdlm_attn_bwd(const bdlm_problem* p,
                           int32_t n_q, const bdlm_range* q_ranges,
@@ -251,11 +246,12 @@ bdlm_status bdlm_attn_bwd(const bdlm_problem* p,
  * bdlm_attn_bwd without a workspace argument, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc).  Same arguments, arithmetic, kernels and results as
- * bdlm_attn_bwd; D and LSE * log2(e) live in a library-owned device array of
+ * bdlm_attn_bwd; the workspace is a library-owned device array of
  * BDLM_NOALLOC_SCRATCH_BYTES bytes instead (one per GPU, held until the process
- * ends).  The call allocates nothing.  Query ranges that need more than the
- * array holds (bdlm_attn_bwd_workspace_bytes() > BDLM_NOALLOC_SCRATCH_BYTES,
- * i.e. more than about 8M (batch x row x head) entries) are rejected with
+ * ends; where it has no room for the partial sums of cut walks, they stay
+ * whole).  The call allocates nothing.  Query ranges whose D and LSE * log2(e)
+ * need more than the array holds (more than about 8M (batch x row x head)
+ * entries) are rejected with
  * BDLM_ERR_UNSUPPORTED before anything is enqueued.  The array of the device
  * current at the call is used, so `stream` must belong to that device.  Every
  * call on one GPU shares its array: calls that overlap in time on one GPU

@@ -24,7 +24,7 @@ __all__ = [
     "BF16", "F32", "CLEAN", "CORRUPTED", "CLEAN_INTRA_CAUSAL", "CLEAN_INTRA_BLOCK",
     "HILO_PV", "HILO_DKDV", "HILO_DQ", "HILO_ALL", "HILO_ADAPTIVE",
     "make_problem", "joint_ranges", "attn_fwd", "attn_partial_fwd", "lse_merge",
-    "attn_bwd_workspace_bytes", "attn_bwd_split_workspace_bytes", "attn_bwd", "attn_bwd_noalloc", "visible_pairs",
+    "attn_bwd_workspace_bytes", "attn_bwd", "attn_bwd_noalloc", "visible_pairs",
     "joint_fwd", "joint_bwd", "timing_enable", "timing_collect", "useful_flops",
 ]
 
@@ -98,9 +98,6 @@ def lib() -> ctypes.CDLL:
                                              ctypes.c_int32, ctypes.c_int64, _VP]
         L.bdlm_attn_bwd_workspace_bytes.argtypes = [ctypes.POINTER(Problem), ctypes.c_int32, ctypes.POINTER(Range)]
         L.bdlm_attn_bwd_workspace_bytes.restype = ctypes.c_size_t
-        L.bdlm_attn_bwd_split_workspace_bytes.argtypes = [ctypes.POINTER(Problem), ctypes.c_int32,
-                                                          ctypes.POINTER(Range), ctypes.c_int32, ctypes.POINTER(Range)]
-        L.bdlm_attn_bwd_split_workspace_bytes.restype = ctypes.c_size_t
         L.bdlm_attn_bwd.argtypes = [ctypes.POINTER(Problem), ctypes.c_int32, ctypes.POINTER(Range), _PP, _PP, _PP,
                                     _PP, _PP, ctypes.c_int32, ctypes.POINTER(Range), _PP, _PP, _PP, _PP,
                                     _VP, ctypes.c_size_t, _VP]
@@ -261,14 +258,8 @@ def attn_bwd_workspace_bytes(p: Problem, q_ranges: Sequence[Range]) -> int:
     return int(lib().bdlm_attn_bwd_workspace_bytes(ctypes.byref(p), len(q_ranges), _rarr(q_ranges)))
 
 
-def attn_bwd_split_workspace_bytes(p: Problem, q_ranges: Sequence[Range], k_ranges: Sequence[Range]) -> int:
-    """Workspace with which :func:`attn_bwd` may also cut long dK/dV walks (small problems)."""
-    return int(lib().bdlm_attn_bwd_split_workspace_bytes(ctypes.byref(p), len(q_ranges), _rarr(q_ranges),
-                                                         len(k_ranges), _rarr(k_ranges)))
-
-
 def attn_bwd(p: Problem, q_ranges, q, o, lse, dO, dq, k_ranges, k, v, dk, dv, workspace, stream=None):
-    """``bdlm_attn_bwd``; ``workspace`` is a device tensor of at least ``attn_bwd_workspace_bytes`` bytes."""
+    """``bdlm_attn_bwd``; ``workspace`` is a device tensor of ``attn_bwd_workspace_bytes`` bytes."""
     nbytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(lib().bdlm_attn_bwd(ctypes.byref(p), len(q_ranges), _rarr(q_ranges), _parr(q), _parr(o), _parr(lse),
                                _parr(dO), _parr(dq), len(k_ranges), _rarr(k_ranges), _parr(k), _parr(v),
@@ -411,7 +402,7 @@ def joint_bwd(q, k, v, o, lse, do, block_size: int, clean_intra: int = CLEAN_INT
         _on_device(q.device, dq=out[0], dk=out[1], dv=out[2])
     dq, dk, dv = out
     if workspace is None:
-        workspace = torch.empty(attn_bwd_split_workspace_bytes(p, r, r), dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(attn_bwd_workspace_bytes(p, r), dtype=torch.uint8, device=q.device)
         if stream is not None:  # used on that stream after this call has dropped it
             workspace.record_stream(torch.cuda.ExternalStream(_stream(stream), device=q.device))
     lp = [lse.data_ptr(), lse.data_ptr() + L * 4]

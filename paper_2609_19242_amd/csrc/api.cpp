@@ -206,86 +206,129 @@ int bf16_query_rows(const bdlm_problem* p, int n_k, const bdlm_range* k_ranges, 
 // How the dK/dV walks of a backward are cut (SplitArgs).  A key tile's walk
 // covers the queries that see it: every query for the first clean keys, one
 // block for corrupted keys.  With few (batch, KV head, tile) workgroups the
-// longest walk, not the card, sets the kernel's time; cutting walks into
-// pieces of half the average load per CU (at least min_unit steps, below which
-// a workgroup's fixed cost and its partial sums outweigh the balance) brings
-// the kernel near the average.  Calls whose longest walk is below that
-// average are left whole.
+// longest walk, not the card, sets the kernel's time.  Walks longer than the
+// average load per CU are then cut into chunks of that length (fp32: a quarter
+// of it, as its workgroups are lighter), at least min_unit steps, below which
+// a workgroup's fixed cost and its partial sums outweigh the balance.
+// Measured: 2,040 tokens, 32/8 heads: dK/dV 375 -> 207 us, and 12 us for the
+// sums (half the average per chunk: 210 and 17; min_unit 16 and 64: no
+// better); 8K, 32/4 heads, adaptive two-term products: 5.5 -> 3.4 ms (half the
+// average: 3.7).  Calls whose longest walk is below the average stay whole.
 struct SplitPlan {
   SplitArgs s;
   size_t counts_bytes = 0, bytes = 0;  // of the workspace: counts, counts + partials
 };
 constexpr int kCus = 256;
 constexpr size_t kMaxSplitBytes = (size_t)256 << 20;
-constexpr int kMinUnitF32 = 8;
+constexpr int kMinUnitF32 = 8, kMinUnitBf16 = 32;
 
-// Calls whose dK/dV kernel takes chunks.
-bool can_split(const bdlm_problem* p, int, const bdlm_range*) { return p->dtype == BDLM_F32; }
+// Does the scheduled dK/dV kernel run this call?
+bool scheduled_dkdv(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges) {
+  int n_q_rows = 0;  // query ranges with rows (empty ones add no work to dK/dV)
+  for (int i = 0; i < n_q; ++i) n_q_rows += q_ranges[i].len > 0 ? 1 : 0;
+  return dkdv_uses_scheduled_kernel(p->dtype == BDLM_BF16, p->head_dim, p->hilo, p->heads / p->kv_heads, n_q_rows);
+}
 
+int key_tile_rows(const bdlm_problem* p) { return p->dtype == BDLM_F32 ? kRowsF32 : kBwdKeysBf16; }
+
+// Steps of the walk of the keys [first, last] of a stream (an upper bound with
+// a clean-context table, which lies in device memory: it may let every
+// corrupted query see a clean key).
+int64_t walk_steps(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges, int stream, int64_t first,
+                   int64_t last) {
+  const bool f32 = p->dtype == BDLM_F32;
+  const int step = f32 ? kRowsF32 : 32;
+  const int64_t group = p->heads / p->kv_heads, per_block = f32 ? group : group / 2;
+  const MaskRule rule = host_rule(p, nullptr);
+  int64_t n = 0;
+  for (int i = 0; i < n_q; ++i) {
+    const bdlm_range& qr = q_ranges[i];
+    int lo, hi, lo1, hi1;
+    query_interval(qr.stream, stream, (int)first, rule, lo, hi);
+    query_interval(qr.stream, stream, (int)last, rule, lo1, hi1);
+    if (p->clean_prefix && stream == BDLM_CLEAN && qr.stream == BDLM_CORRUPTED) {
+      lo = 0;
+      hi1 = kBig;
+    }
+    const int64_t u0 = std::max<int64_t>(lo - qr.pos0, 0), u1 = std::min<int64_t>(hi1 - qr.pos0, qr.len);
+    if (u1 > u0) n += ((u1 + step - 1) / step - u0 / step) * per_block;
+  }
+  return n;
+}
+
+// The chunks of a call's key ranges at `unit` steps each (0: whole walks).
 SplitPlan split_plan(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges, int n_k, const bdlm_range* k_ranges,
-                     bool enable) {
+                     int64_t unit) {
   SplitPlan pl;
   pl.s = SplitArgs{};
-  pl.s.unit = 1;
-  const bool f32 = p->dtype == BDLM_F32;
-  const int tile = f32 ? kRowsF32 : kBwdKeysBf16, step = f32 ? kRowsF32 : 32;
-  const int64_t pairs = (int64_t)p->kv_heads * p->batch, group = p->heads / p->kv_heads;
-  int64_t tiles = 0;
-  for (int j = 0; j < n_k; ++j) {
-    pl.s.chunks[j] = 1;
-    tiles += (k_ranges[j].len + tile - 1) / tile;
-  }
-  pl.s.wgs_per_pair = (int32_t)tiles;
-  // (enough workgroups: the average over them is what each CU gets anyway)
-  if (!enable || tiles * pairs > 16 * kCus) return pl;
-  // Walk lengths; a clean-context table (in device memory) may let every query see a clean key.
-  const MaskRule rule = host_rule(p, nullptr);
-  int64_t total = 0, longest = 0, walk[kMaxK] = {};
+  pl.s.unit = (int32_t)std::max<int64_t>(unit, 1);
+  const int tile = key_tile_rows(p);
+  const int64_t pairs = (int64_t)p->kv_heads * p->batch;
+  int64_t wgs = 0, slots = 0, chunked = 0;
   for (int j = 0; j < n_k; ++j) {
     const bdlm_range& kr = k_ranges[j];
-    for (int64_t k0 = 0; k0 < kr.len; k0 += tile) {
-      const int first = (int)(kr.pos0 + k0), last = (int)(kr.pos0 + std::min<int64_t>(k0 + tile, kr.len) - 1);
-      int64_t n = 0;
-      for (int i = 0; i < n_q; ++i) {
-        const bdlm_range& qr = q_ranges[i];
-        int lo, hi, lo1, hi1;
-        query_interval(qr.stream, kr.stream, first, rule, lo, hi);
-        query_interval(qr.stream, kr.stream, last, rule, lo1, hi1);
-        if (p->clean_prefix && kr.stream == BDLM_CLEAN && qr.stream == BDLM_CORRUPTED) {
-          lo = 0;
-          hi1 = kBig;
-        }
-        const int64_t u0 = std::max<int64_t>(lo - qr.pos0, 0), u1 = std::min<int64_t>(hi1 - qr.pos0, qr.len);
-        if (u1 > u0) n += ((u1 + step - 1) / step - u0 / step) * group;
-      }
-      walk[j] = std::max(walk[j], n);
+    const int64_t nt = (kr.len + tile - 1) / tile;
+    int64_t walk = 0;
+    if (unit > 0)
+      for (int64_t t = 0; t < nt; ++t)
+        walk = std::max(walk, walk_steps(p, n_q, q_ranges, kr.stream, kr.pos0 + t * tile,
+                                         kr.pos0 + std::min<int64_t>((t + 1) * tile, kr.len) - 1));
+    const int64_t ch = unit > 0 ? std::max<int64_t>((walk + unit - 1) / unit, 1) : 1;
+    pl.s.chunks[j] = (int32_t)ch;
+    wgs += nt * ch;
+    if (ch > 1) {
+      slots += nt * ch;
+      chunked += nt;
+    }
+  }
+  pl.s.wgs_per_pair = (int32_t)wgs;
+  pl.s.tiles_per_pair = (int32_t)chunked;
+  pl.s.slots_per_pair = (int32_t)slots;
+  const size_t slot = (size_t)2 * tile * p->head_dim * (p->dtype == BDLM_F32 ? sizeof(double) : sizeof(float));
+  pl.counts_bytes = align256((size_t)(slots * pairs) * sizeof(int32_t));
+  pl.bytes = slots == 0 ? 0 : pl.counts_bytes + (size_t)(slots * pairs) * slot;
+  return pl;
+}
+
+// Steps per chunk (0: walks stay whole), and the workspace bytes the chunks of
+// a joint call's keys (every position of both streams) need.  The decision
+// takes the problem and its queries only, so that a key range's dK and dV do
+// not depend on which other key ranges are in the call.
+int64_t split_unit(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges, size_t* bytes) {
+  *bytes = 0;
+  const bool f32 = p->dtype == BDLM_F32;
+  if (!f32 && !scheduled_dkdv(p, n_q, q_ranges)) return 0;
+  const int tile = key_tile_rows(p);
+  const int64_t pairs = (int64_t)p->kv_heads * p->batch, tiles = (p->L + tile - 1) / tile;
+  if (tiles * pairs > 16 * kCus) return 0;  // the average over so many is what each CU gets anyway
+  int64_t total = 0, longest = 0;
+  for (int stream : {BDLM_CLEAN, BDLM_CORRUPTED})
+    for (int64_t t = 0; t < tiles; ++t) {
+      const int64_t n =
+          walk_steps(p, n_q, q_ranges, stream, t * tile, std::min<int64_t>((t + 1) * tile, p->L) - 1);
+      longest = std::max(longest, n);
       total += n * pairs;
     }
-    longest = std::max(longest, walk[j]);
-  }
   const int64_t average = total / kCus;
-  if (longest <= average) return pl;
-  for (int64_t unit = std::max<int64_t>(kMinUnitF32, average / 2);; unit *= 2) {
-    int64_t wgs = 0, slots = 0, chunked = 0;
-    for (int j = 0; j < n_k; ++j) {
-      const int64_t nt = (k_ranges[j].len + tile - 1) / tile;
-      const int64_t ch = std::max<int64_t>((walk[j] + unit - 1) / unit, 1);
-      pl.s.chunks[j] = (int32_t)ch;
-      wgs += nt * ch;
-      if (ch > 1) {
-        slots += nt * ch;
-        chunked += nt;
-      }
-    }
-    pl.s.unit = (int32_t)unit;
-    pl.s.wgs_per_pair = (int32_t)wgs;
-    pl.s.tiles_per_pair = (int32_t)chunked;
-    pl.s.slots_per_pair = (int32_t)slots;
-    const size_t slot = (size_t)2 * tile * p->head_dim * (f32 ? sizeof(double) : sizeof(float));
-    pl.counts_bytes = align256((size_t)(slots * pairs) * sizeof(int32_t));
-    pl.bytes = slots == 0 ? 0 : pl.counts_bytes + (size_t)(slots * pairs) * slot;
-    if (pl.bytes <= kMaxSplitBytes) return pl;
+  const bdlm_range joint[2] = {{BDLM_CLEAN, 0, 0, p->L, 0}, {BDLM_CORRUPTED, 0, 0, p->L, 0}};
+  for (int64_t unit = f32 ? std::max<int64_t>(kMinUnitF32, average / 4) : std::max<int64_t>(kMinUnitBf16, average);
+       longest > average && longest > unit; unit *= 2) {
+    *bytes = split_plan(p, n_q, q_ranges, 2, joint, unit).bytes;
+    if (*bytes <= kMaxSplitBytes) return unit;
   }
+  *bytes = 0;
+  return 0;
+}
+
+// The row statistics' part of the backward workspace.
+size_t stats_bytes(const bdlm_problem* p, int32_t n_q, const bdlm_range* q_ranges) {
+  if (!p || !q_ranges || n_q < 1 || n_q > kMaxQ || p->batch < 1 || p->heads < 1 || p->head_dim < 1) return 0;
+  size_t tot = 0;
+  for (int i = 0; i < n_q; ++i) {
+    const size_t rows = (size_t)p->batch * (size_t)(q_ranges[i].len > 0 ? q_ranges[i].len : 0);
+    tot += 2 * align256(rows * p->heads * sizeof(float));  // LSE * log2(e), then D = rowsum(dO * O)
+  }
+  return tot;
 }
 
 bdlm_status check_grid(int64_t tiles, int64_t mult) {
@@ -419,24 +462,15 @@ bdlm_status bdlm_lse_merge_strided(int64_t batch, int64_t rows, int32_t heads, i
 }
 
 size_t bdlm_attn_bwd_workspace_bytes(const bdlm_problem* p, int32_t n_q, const bdlm_range* q_ranges) {
-  if (!p || !q_ranges || n_q < 1 || n_q > kMaxQ || p->batch < 1 || p->heads < 1 || p->head_dim < 1) return 0;
-  size_t tot = 0;
-  for (int i = 0; i < n_q; ++i) {
-    const size_t rows = (size_t)p->batch * (size_t)(q_ranges[i].len > 0 ? q_ranges[i].len : 0);
-    tot += 2 * align256(rows * p->heads * sizeof(float));  // LSE * log2(e), then D = rowsum(dO * O)
-  }
-  return tot;
-}
-
-size_t bdlm_attn_bwd_split_workspace_bytes(const bdlm_problem* p, int32_t n_q, const bdlm_range* q_ranges,
-                                           int32_t n_k, const bdlm_range* k_ranges) {
-  const size_t base = bdlm_attn_bwd_workspace_bytes(p, n_q, q_ranges);
-  if (check_problem(p) != BDLM_OK || check_counts(n_q, n_k, q_ranges, k_ranges) != BDLM_OK) return base;
-  for (int i = 0; i < n_q; ++i)
-    if (check_range(p, q_ranges[i], "query", i) != BDLM_OK) return base;
-  for (int j = 0; j < n_k; ++j)
-    if (check_range(p, k_ranges[j], "key", j) != BDLM_OK) return base;
-  return base + split_plan(p, n_q, q_ranges, n_k, k_ranges, can_split(p, n_q, q_ranges)).bytes;
+  const size_t base = stats_bytes(p, n_q, q_ranges);
+  if (base == 0) return 0;
+  const std::string err = g_err;  // this query reports no errors
+  bool ok = check_problem(p) == BDLM_OK;
+  for (int i = 0; i < n_q; ++i) ok = ok && check_range(p, q_ranges[i], "query", i) == BDLM_OK;
+  g_err = err;
+  size_t split = 0;
+  if (ok) split_unit(p, n_q, q_ranges, &split);
+  return base + split;
 }
 
 }  // extern "C"
@@ -483,7 +517,7 @@ bdlm_status attn_bwd_impl(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
   if (!q || !o || !lse || !dO || !dq || !k || !v || !dk || !dv) return fail(BDLM_ERR_INVALID, "pointer array is null");
   for (int i = 0; i < n_q; ++i)
     if ((st = check_range(p, q_ranges[i], "query", i)) != BDLM_OK) return st;
-  const size_t need = bdlm_attn_bwd_workspace_bytes(p, n_q, q_ranges);
+  const size_t need = stats_bytes(p, n_q, q_ranges);
   if (use_scratch) {
     if (need > kScratchBytes)
       return fail(BDLM_ERR_UNSUPPORTED,
@@ -498,9 +532,7 @@ bdlm_status attn_bwd_impl(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
   fill_common(a, p);
   a.n_q = n_q;
   a.n_k = n_k;
-  int n_q_rows = 0;  // query ranges with rows (empty ones add no work to dK/dV)
-  for (int i = 0; i < n_q; ++i) n_q_rows += q_ranges[i].len > 0 ? 1 : 0;
-  a.stats_form = dkdv_uses_scheduled_kernel(p->dtype == BDLM_BF16, p->head_dim, p->hilo, a.group, n_q_rows) ? 1 : 0;
+  a.stats_form = scheduled_dkdv(p, n_q, q_ranges) ? 1 : 0;
   size_t ws_off[kMaxQ] = {};
   size_t off = 0;
   for (int i = 0; i < n_q; ++i) {
@@ -545,8 +577,10 @@ bdlm_status attn_bwd_impl(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
   if ((st = check_grid(tiles, (int64_t)p->kv_heads * p->batch)) != BDLM_OK) return st;
   a.total_tiles = (int32_t)tiles;
   // Long walks are cut when the workspace has room for the partial sums behind the row statistics.
-  SplitPlan plan = split_plan(p, n_q, q_ranges, n_k, k_ranges, !use_scratch && can_split(p, n_q, q_ranges));
-  if (plan.bytes > 0 && workspace_bytes < need + plan.bytes) plan = split_plan(p, n_q, q_ranges, n_k, k_ranges, false);
+  size_t joint_bytes = 0;
+  const size_t room = (use_scratch ? kScratchBytes : std::max(workspace_bytes, need)) - need;
+  SplitPlan plan = split_plan(p, n_q, q_ranges, n_k, k_ranges, split_unit(p, n_q, q_ranges, &joint_bytes));
+  if (plan.bytes > room) plan = split_plan(p, n_q, q_ranges, n_k, k_ranges, 0);
   a.split = plan.s;
   // The dQ kernel walks query tiles (of its own height).
   AttnArgs aq = a;
@@ -608,6 +642,10 @@ bdlm_status attn_bwd_impl(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
       return launch_bwd_dkdv(ak, stream);
     });
     if (e != hipSuccess) return hip_fail(e, "backward dK/dV launch");
+    if (plan.bytes > 0) {
+      e = timed(kKBwdSum, stream, [&] { return launch_bwd_dkdv_sum(a, stream); });
+      if (e != hipSuccess) return hip_fail(e, "backward dK/dV sum launch");
+    }
   } else {
     // The dQ kernel leaves D in the workspace for the dK/dV kernel.
     e = timed(kKBwdDqF32, stream, [&] { return launch_bwd_dq_f32(aq, p->head_dim, stream); });

@@ -42,6 +42,7 @@
 // products use VGPR accumulators, which the softmax reads).
 #include "common.hpp"
 #include "device.hpp"
+#include "ktiles.hpp"
 
 namespace bdlm {
 
@@ -163,22 +164,10 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   const int G = lane >> 4, sl = lane & 15;
   const int64_t H = a.heads, HKV = a.kv_heads;
 
-  // ---- work item: (batch, KV head, key range, key tile); heaviest tiles first per XCD
-  const int T = a.total_tiles;
-  int bk, order;
-  if (!xcd_pair_item(blockIdx.x, a.kv_heads * a.batch, T, true, bk, order)) return;
-  const int b = bk / a.kv_heads, kvh = bk - (bk / a.kv_heads) * a.kv_heads;
-  int r = a.order[0], t = order;
-  for (int n = 0; n < a.n_k; ++n) {
-    const int rr = a.order[n];
-    const int nt = a.kr[rr].ntiles;
-    if (order < nt) {
-      r = rr;
-      t = order;
-      break;
-    }
-    order -= nt;
-  }
+  // ---- work item: (batch, KV head, key range, key tile, chunk of its walk); heaviest tiles first per XCD
+  KeyTileItem it;
+  if (!key_tile_item(a, blockIdx.x, it)) return;
+  const int b = it.b, kvh = it.kvh, r = it.r, t = it.t;
   const KRangeArg& kr = a.kr[r];
   const int key0 = t * BN;
   const int nk = imin(BN, kr.len - key0);
@@ -259,8 +248,14 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   auto sel2 = [](int q, auto v0, auto v1) { return q ? v1 : v0; };
 #define BDLM_PICK(f, q) sel2((q), R0.f, R1.f)
   // The walk by step index (walk_plan, walk_step).
-  const WalkPlan wp = walk_plan(R0.s0, R0.s1, R1.s0, R1.s1, a.group / NH);
-  const int nsteps = wp.nsteps;
+  WalkPlan wp = walk_plan(R0.s0, R0.s1, R1.s0, R1.s1, a.group / NH);
+  // This workgroup's chunk of it: steps [n0, n1).
+  const int max_ch = a.split.chunks[r];
+  const int nch = max_ch > 1 ? chunks_of(wp.nsteps, a.split.unit, max_ch) : 1;
+  if (max_ch > 1 && it.chunk == 0 && tid == 0) a.split.counts[it.slot] = nch;
+  if (it.chunk >= nch) return;
+  const int n0 = it.chunk * a.split.unit, n1 = it.chunk + 1 < nch ? n0 + a.split.unit : wp.nsteps;
+  wp.nsteps = n1;  // (steps past the chunk copy nothing)
 
   // ---- copies.  Instruction i of a wave is instruction (w & 1) * kIPW + i of
   // its tensor; the per-lane global offsets are constant over the walk.
@@ -294,7 +289,7 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
                      lb_0, lb_1);
   };
   StepDesc bt;
-  int bbase = 0;
+  int bbase = n0;
   // Per-lane offsets of the dword copy for each range (rows of two heads).
   const uint32_t lvo0 = (uint32_t)(((lane >> 5) * R0.len + (lane & 31)) * 4);
   const uint32_t lvo1 = (uint32_t)(((lane >> 5) * R1.len + (lane & 31)) * 4);
@@ -452,7 +447,7 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   // its first products, the starts of step `nx` (stage NX) are loaded under its
   // last ones, and the walk advances under the softmax of head 0.
   constexpr int TA = 8;  // transpose-read pairs in flight ahead of the dV/dK products
-  int i0 = 0;    // the current step
+  int i0 = n0;   // the current step
   CopyPlan cpl;  // copies of step i0 + 3, planned during the step before
   auto run_step = [&](auto st_c, auto nx_c, int cp_stage) __attribute__((always_inline)) {
     constexpr int ST = decltype(st_c)::value, NX = decltype(nx_c)::value;
@@ -599,19 +594,19 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   // which the copies issued next overwrite.
   // A batch covers steps bbase .. bbase + 63 and is renewed every 56 steps: an
   // iteration of the loop below starting at step i0 reads steps up to i0 + 7.
-  bt = make_batch(0);
-  cpl = copy_plan(3);
+  bt = make_batch(n0);
+  cpl = copy_plan(n0 + 3);
   plan_ready(cpl);
-  copy_step(0, 0);
-  copy_step(1, 1);
-  copy_step(2, 2);
+  copy_step(0, n0);
+  copy_step(1, n0 + 1);
+  copy_step(2, n0 + 2);
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kIPW + 1) : "memory");  // steps 0 and 1 landed
   // K and V are pinned in AGPRs only now: pinning reads them, so their loads
   // (issued first) are waited for here, after the walk set-up and the first
   // copies, instead of before them.
 #pragma unroll
   for (int s = 0; s < kKS; ++s) asm volatile("" : "+a"(kf[s]), "+a"(vf[s]));
-  load_starts(0, 0);
+  load_starts(0, n0);
 #pragma unroll
   for (int i = 0; i < RA; ++i) {
     nq[i] = lds_load16(yq[i]);
@@ -621,17 +616,17 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   using I1 = std::integral_constant<int, 1>;
   using I2 = std::integral_constant<int, 2>;
   using I3 = std::integral_constant<int, 3>;
-  while (i0 < nsteps) {
+  while (i0 < n1) {
     if (i0 - bbase >= 56) {
       bbase = i0;
       bt = make_batch(bbase);
     }
     run_step(I0{}, I1{}, 3);
-    if (i0 >= nsteps) break;
+    if (i0 >= n1) break;
     run_step(I1{}, I2{}, 0);
-    if (i0 >= nsteps) break;
+    if (i0 >= n1) break;
     run_step(I2{}, I3{}, 1);
-    if (i0 >= nsteps) break;
+    if (i0 >= n1) break;
     run_step(I3{}, I0{}, 2);
   }
   // Copies still in flight target stages nobody reads; they must land before
@@ -643,7 +638,23 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   // ---- epilogue: dK = scale dK^T^T, dV (bf16 or fp32); unseen keys get zeros
 #pragma unroll
   for (int d = 0; d < kDT; ++d) asm volatile("" : "+a"(dka[d]), "+a"(dva[d]));
-  if (a.out_f32) {
+  if (nch > 1) {
+    // The chunk's partial sums, in register order (whole cache lines per store).
+    f32x4* pp = (f32x4*)a.split.partials + ((it.slot + it.chunk) * 4 + w) * (2 * kDT * 4 * 64) + lane;
+#pragma unroll
+    for (int d = 0; d < kDT; ++d)
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        f32x4 vk, vv;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          vk[e] = dka[d][4 * g4 + e];
+          vv[e] = dva[d][4 * g4 + e];
+        }
+        pp[(4 * d + g4) * 64] = vk;
+        pp[(4 * kDT + 4 * d + g4) * 64] = vv;
+      }
+  } else if (a.out_f32) {
     if (key_ok) {
       const int64_t off = (((int64_t)b * kr.bstride + key0 + mykey) * HKV + kvh) * kD;
       float* dkp = (float*)kr.dk + off;
@@ -697,10 +708,58 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   }
 }
 
+// dK, dV of the chunked key tiles: the chunks' partial sums added in chunk
+// order.  A thread owns 8 consecutive head_dim elements of one key of dK or
+// dV, two 16-byte pieces of each partial; kSumWgs workgroups per tile.  HBM
+// (mostly L2 and MALL) traffic: the partials once.
+constexpr int kSumWgs = 4 * 2 * kDT * 4 * 32 / 256;
+__global__ __launch_bounds__(256) void dkdv_sum_kernel(const AttnArgs a) {
+  SumItem it;
+  sum_item(a, blockIdx.x / kSumWgs, it);
+  const int nch = a.split.counts[it.slot];
+  if (nch <= 1) return;
+  const int n = (blockIdx.x % kSumWgs) * 256 + threadIdx.x;
+  const int l32 = n & 31, piece = (n >> 5) & (2 * kDT * 4 - 1), w = n >> 10;  // piece: dK's 4 d + g4, then dV's
+  static_assert(2 * kDT * 4 == 32, "index split");
+  const f32x4* pp = (const f32x4*)a.split.partials + (it.slot * 4 + w) * (2 * kDT * 4 * 64) + piece * 64 + l32;
+  f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+  for (int ch = 0; ch < nch; ++ch) {
+    lo += pp[0];
+    hi += pp[32];
+    pp += 4 * 2 * kDT * 4 * 64;
+  }
+  const KRangeArg& kr = a.kr[it.r];
+  const int key = it.t * kBwdKeysBf16 + w * 32 + l32;
+  if (key >= kr.len) return;
+  const bool is_dv = piece >= 4 * kDT;
+  const float sc = is_dv ? 1.f : a.scale;
+  const int64_t off = (((int64_t)it.b * kr.bstride + key) * a.kv_heads + it.kvh) * kD + (piece & (4 * kDT - 1)) * 8;
+  void* out = is_dv ? kr.dv : kr.dk;
+  if (a.out_f32) {
+    *(f32x4*)((float*)out + off) = lo * sc;
+    *(f32x4*)((float*)out + off + 4) = hi * sc;
+  } else {
+    bf16x8 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = to_bf16(lo[e] * sc);
+      v[4 + e] = to_bf16(hi[e] * sc);
+    }
+    *(bf16x8*)((bf16*)out + off) = v;
+  }
+}
+
 }  // namespace
 
+hipError_t launch_bwd_dkdv_sum(const AttnArgs& a, hipStream_t s) {
+  const int n = a.split.tiles_per_pair * a.kv_heads * a.batch * kSumWgs;
+  if (n == 0) return hipSuccess;
+  hipLaunchKernelGGL(dkdv_sum_kernel, dim3(n), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_bwd_dkdv(const AttnArgs& a, hipStream_t s) {
-  const int n = workgroups_for(a.total_tiles * a.kv_heads * a.batch);
+  const int n = workgroups_for(a.split.wgs_per_pair * a.kv_heads * a.batch);
   if (n == 0) return hipSuccess;
   // two query heads per step, at most two query ranges (the walk state stays in registers)
   if (a.group % 2 != 0 || a.n_q > 2) return hipErrorInvalidValue;

@@ -22,6 +22,7 @@
 // kernels together: L = 256, 2/2 heads, d 64: 10.7 ms -> 44 us; L = 1125, 8/2
 // heads, d 128: 621 -> 0.71 ms.
 #include "f64tile.hpp"
+#include "ktiles.hpp"
 #include "qtiles.hpp"
 
 namespace bdlm {
@@ -139,34 +140,6 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
       *(fl4*)(out + 4 * e4) = o;
     }
   }
-}
-
-// The key tile of a workgroup of the dK/dV kernel: tiles of a (batch, KV head)
-// pair in visiting order (heaviest range first), a tile's chunks one after the
-// other.
-struct KeyTileItem {
-  int b, kvh, r, t, chunk;
-  int64_t slot;  // index of the tile's chunk 0 in the partials (chunked ranges)
-};
-__device__ inline bool key_tile_item(const AttnArgs& a, int wg, KeyTileItem& it) {
-  int bk, rank;
-  if (!xcd_pair_item(wg, a.kv_heads * a.batch, a.split.wgs_per_pair, true, bk, rank)) return false;
-  it.b = bk / a.kv_heads;
-  it.kvh = bk - it.b * a.kv_heads;
-  it.r = a.order[0];
-  int64_t base = 0;
-  for (int n = 0; n < a.n_k; ++n) {
-    const int r = a.order[n], ch = a.split.chunks[r], nw = a.kr[r].ntiles * ch;
-    it.r = r;
-    if (rank < nw) break;
-    rank -= nw;
-    if (ch > 1) base += nw;
-  }
-  const int ch = a.split.chunks[it.r];
-  it.t = rank / ch;
-  it.chunk = rank - it.t * ch;
-  it.slot = (int64_t)bk * a.split.slots_per_pair + base + (int64_t)it.t * ch;
-  return true;
 }
 
 template <int D>
@@ -331,32 +304,20 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
 template <int D>
 __global__ __launch_bounds__(256) void bwd_sum_f32_kernel(const AttnArgs a) {
   constexpr int OPS = 16 * D, EPT = OPS / 256;
-  int tile = blockIdx.x % a.split.tiles_per_pair;
-  const int bk = blockIdx.x / a.split.tiles_per_pair;
-  const int b = bk / a.kv_heads, kvh = bk - b * a.kv_heads;
-  int r = a.order[0];
-  int64_t slot = (int64_t)bk * a.split.slots_per_pair;
-  for (int n = 0; n < a.n_k; ++n) {
-    r = a.order[n];
-    const int ch = a.split.chunks[r];
-    if (ch <= 1) continue;
-    if (tile < a.kr[r].ntiles) break;
-    tile -= a.kr[r].ntiles;
-    slot += (int64_t)a.kr[r].ntiles * ch;
-  }
-  const KRangeArg& kr = a.kr[r];
-  slot += (int64_t)tile * a.split.chunks[r];
-  const int nch = a.split.counts[slot];
+  SumItem it;
+  sum_item(a, blockIdx.x, it);
+  const KRangeArg& kr = a.kr[it.r];
+  const int nch = a.split.counts[it.slot];
   if (nch <= 1) return;
-  const int nvalid = imin(16, kr.len - tile * 16);
+  const int nvalid = imin(16, kr.len - it.t * 16);
   const int k = threadIdx.x / (D / EPT), d0 = (threadIdx.x % (D / EPT)) * EPT;
   if (k >= nvalid) return;
-  const int64_t off = (((int64_t)b * kr.bstride + tile * 16 + k) * a.kv_heads + kvh) * D + d0;
+  const int64_t off = (((int64_t)it.b * kr.bstride + it.t * 16 + k) * a.kv_heads + it.kvh) * D + d0;
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
     double x[EPT] = {};
     for (int ch = 0; ch < nch; ++ch) {
-      const double* src = (const double*)a.split.partials + ((slot + ch) * 2 + which) * OPS + k * D + d0;
+      const double* src = (const double*)a.split.partials + ((it.slot + ch) * 2 + which) * OPS + k * D + d0;
 #pragma unroll
       for (int e = 0; e < EPT; ++e) x[e] += src[e];
     }

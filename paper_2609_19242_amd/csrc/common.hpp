@@ -244,6 +244,7 @@ hipError_t launch_fwd_f32(const AttnArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_merge(const MergeArgs& a, int head_dim, int part_dtype, int out_dtype, hipStream_t s);
 hipError_t launch_bwd_bf16(const AttnArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_bwd_dkdv(const AttnArgs& a, hipStream_t s);
+hipError_t launch_bwd_dkdv_sum(const AttnArgs& a, hipStream_t s);
 hipError_t launch_bwd_dq_bf16(const AttnArgs& a, int head_dim, int rows, hipStream_t s);
 hipError_t launch_bwd_dq_f32(const AttnArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_bwd_dkv_f32(const AttnArgs& a, int head_dim, hipStream_t s);
