@@ -226,7 +226,7 @@ constexpr int kMinUnitF32 = 8, kMinUnitBf16 = 32;
 bool scheduled_dkdv(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges) {
   int n_q_rows = 0;  // query ranges with rows (empty ones add no work to dK/dV)
   for (int i = 0; i < n_q; ++i) n_q_rows += q_ranges[i].len > 0 ? 1 : 0;
-  return dkdv_uses_scheduled_kernel(p->dtype == BDLM_BF16, p->head_dim, p->hilo, p->heads / p->kv_heads, n_q_rows);
+  return dkdv_uses_scheduled_kernel(p->dtype == BDLM_BF16, p->hilo, n_q_rows);
 }
 
 int key_tile_rows(const bdlm_problem* p) { return p->dtype == BDLM_F32 ? kRowsF32 : kBwdKeysBf16; }
@@ -237,8 +237,9 @@ int key_tile_rows(const bdlm_problem* p) { return p->dtype == BDLM_F32 ? kRowsF3
 int64_t walk_steps(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges, int stream, int64_t first,
                    int64_t last) {
   const bool f32 = p->dtype == BDLM_F32;
-  const int step = f32 ? kRowsF32 : 32;
-  const int64_t group = p->heads / p->kv_heads, per_block = f32 ? group : group / 2;
+  // a step: 16 rows of one head (fp32), 32 rows of two heads, or 64 rows of one head (odd groups)
+  const int64_t group = p->heads / p->kv_heads, per_block = f32 || group % 2 ? group : group / 2;
+  const int step = f32 ? kRowsF32 : group % 2 ? 64 : 32;
   const MaskRule rule = host_rule(p, nullptr);
   int64_t n = 0;
   for (int i = 0; i < n_q; ++i) {
@@ -309,7 +310,8 @@ int64_t split_unit(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges, s
       longest = std::max(longest, n);
       total += n * pairs;
     }
-  const int64_t average = total / kCus;
+  // (workgroups that fit a CU side by side: two at head_dim 64, bf16)
+  const int64_t average = total / (!f32 && p->head_dim == 64 ? 2 * kCus : kCus);
   const bdlm_range joint[2] = {{BDLM_CLEAN, 0, 0, p->L, 0}, {BDLM_CORRUPTED, 0, 0, p->L, 0}};
   for (int64_t unit = f32 ? std::max<int64_t>(kMinUnitF32, average / 4) : std::max<int64_t>(kMinUnitBf16, average);
        longest > average && longest > unit; unit *= 2) {
@@ -639,11 +641,11 @@ bdlm_status attn_bwd_impl(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
       ak.n_q = 0;
       for (int i = 0; i < n_q; ++i)
         if (a.qr[i].len > 0) ak.qr[ak.n_q++] = a.qr[i];
-      return launch_bwd_dkdv(ak, stream);
+      return launch_bwd_dkdv(ak, p->head_dim, stream);
     });
     if (e != hipSuccess) return hip_fail(e, "backward dK/dV launch");
     if (plan.bytes > 0) {
-      e = timed(kKBwdSum, stream, [&] { return launch_bwd_dkdv_sum(a, stream); });
+      e = timed(kKBwdSum, stream, [&] { return launch_bwd_dkdv_sum(a, p->head_dim, stream); });
       if (e != hipSuccess) return hip_fail(e, "backward dK/dV sum launch");
     }
   } else {

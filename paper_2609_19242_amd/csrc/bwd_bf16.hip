@@ -1,4 +1,5 @@
-// dK and dV of the BDLM attention backward, key-major, bf16 inputs, fp32 accumulation, gfx950.
+// dK and dV of the BDLM attention backward, key-major, bf16 inputs, fp32 accumulation, gfx950: the general
+// kernel, for calls with more than two query ranges or two-term products on every step (bwd_dkdv.hip has the rest).
 //
 // Exact gradients from the saved O and LSE (arXiv 2609.19242 App. C fused
 // backward; eq:correctness-corrupted-gradient and eq:correctness-clean-gradient):
@@ -585,25 +586,31 @@ void launch_nh(const AttnArgs& a, int n, hipStream_t s) {
     hipLaunchKernelGGL((bwd_bf16_kernel<D, HM, 1, NQ>), dim3(n), dim3(256), 0, s, a);
 }
 
+// (single-term and adaptive products of at most two query ranges run in bwd_dkdv.hip)
 template <int D, int HM>
-void launch_nq(const AttnArgs& a, int n, hipStream_t s) {
-  if (a.n_q <= 2) launch_nh<D, HM, 2>(a, n, s);
-  else launch_nh<D, HM, kMaxQ>(a, n, s);
+hipError_t launch_nq(const AttnArgs& a, int n, hipStream_t s) {
+  if constexpr (HM == 1) {
+    if (a.n_q <= 2) {
+      launch_nh<D, HM, 2>(a, n, s);
+      return hipGetLastError();
+    }
+  }
+  if (a.n_q <= 2) return hipErrorInvalidValue;
+  launch_nh<D, HM, kMaxQ>(a, n, s);
+  return hipGetLastError();
 }
 
 template <int D>
-void launch_hm(const AttnArgs& a, int n, hipStream_t s) {
-  if (!(a.hilo & kHiloDkDv)) launch_nq<D, 0>(a, n, s);
-  else if (!(a.hilo & kHiloAdaptive)) launch_nq<D, 1>(a, n, s);
-  else launch_nq<D, 2>(a, n, s);
+hipError_t launch_hm(const AttnArgs& a, int n, hipStream_t s) {
+  if (!(a.hilo & kHiloDkDv)) return launch_nq<D, 0>(a, n, s);
+  if (!(a.hilo & kHiloAdaptive)) return launch_nq<D, 1>(a, n, s);
+  return launch_nq<D, 2>(a, n, s);
 }
 
 hipError_t launch_bwd_bf16(const AttnArgs& a, int head_dim, hipStream_t s) {
   const int n = workgroups_for(a.total_tiles * a.kv_heads * a.batch);
   if (n == 0) return hipSuccess;
-  if (head_dim == 128) launch_hm<128>(a, n, s);
-  else launch_hm<64>(a, n, s);
-  return hipGetLastError();
+  return head_dim == 128 ? launch_hm<128>(a, n, s) : launch_hm<64>(a, n, s);
 }
 
 }  // namespace bdlm

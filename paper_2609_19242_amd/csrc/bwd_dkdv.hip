@@ -1,5 +1,6 @@
 // dK and dV of the BDLM attention backward, key-major, bf16 inputs, fp32
-// accumulation, head_dim 128, gfx950: the software-pipelined kernel.
+// accumulation, gfx950: the software-pipelined kernel (single-term or adaptive
+// two-term products, at most two query ranges).
 //
 // Exact gradients from the saved O and LSE (arXiv 2609.19242 App. C fused
 // backward; eq:correctness-corrupted-gradient and eq:correctness-clean-gradient):
@@ -8,15 +9,17 @@
 // summed over every query row that sees a key and over the query heads of the
 // key's GQA group.  dQ comes from the query-major kernel (bwd_dq.hip).
 //
-// Work split as in bwd_bf16.hip: a workgroup owns 128 keys of one KV head (4
-// waves x 32 keys, one wave per SIMD), holds their K and V rows in AGPRs as
-// MFMA operands and accumulates dK^T and dV^T in AGPRs over the whole walk of
-// visible 32-row query steps (every query range, two query heads per step).
+// A workgroup owns 128 keys of one KV head (4 waves x 32 keys), holds their K
+// and V rows in AGPRs as MFMA operands and accumulates dK^T and dV^T in AGPRs
+// over its walk (or chunk of a walk, ktiles.hpp) of visible query steps.  A
+// step is two sub-blocks of 32 query rows: the same rows of two query heads of
+// an even GQA group, or 64 rows of one head of an odd one.
 //
-// What differs is the schedule of a step.  With one wave per SIMD nothing
+// At head_dim 128 one wave per SIMD fits (384 registers), and nothing else
 // hides a wave's own dependency chain S, dP -> softmax -> dV, dK, so the step
-// is written as four blocks of 16 matrix products each, with the vector and
-// scalar work placed under them and the order fixed by scheduling fences:
+// is written as four blocks of 16 matrix products each (8 at head_dim 64),
+// with the vector and scalar work placed under them and the order fixed by
+// scheduling fences (heads 0, 1 here: the sub-blocks):
 //   A: S_0 = Q_0 K^T, dP_0 = dO_0 V^T (head 0)  under  the LDS-DMA copies of
 //      the step three ahead and the copy plan of the step after
 //   B: S_1, dP_1 (head 1)      under  P_0 = exp2(c S_0), dS_0 = P_0 dP_0, and
@@ -25,7 +28,8 @@
 //   D: dV += dO_1^T P_1, dK += Q_1^T dS_1   under  dS_1 = P_1 dP_1, the next
 //      step's accumulator starts, and its first row reads (issued before the
 //      step's barrier: that stage is complete from the barrier before)
-// Row operands are read four products ahead, transpose operands eight.  The
+// Row operands are read four products ahead, transpose operands eight (at
+// head_dim 64 two and four: 242 registers, so two workgroups share a CU).  The
 // walk's bookkeeping is vector work: the descriptors of 64 steps (block,
 // range, partial flag, copy resource words) sit in the lanes of a few VGPRs,
 // computed every 56 steps from a closed form (walk_plan, walk_step), and a
@@ -40,6 +44,10 @@
 // before every LDS transpose read (it cannot tell which stage a DMA writes).
 // The dV/dK products are inline-assembly MFMAs on AGPR accumulators (the S/dP
 // products use VGPR accumulators, which the softmax reads).
+// Bound by the matrix cores (and, at head_dim 64, the exponentials: one per
+// product).  Measured against the general kernel of bwd_bf16.hip: 4K, batch 2,
+// 32/8 heads, head_dim 64: 790 -> 590 us (whole walks 630; one wave per SIMD
+// with the longer read-ahead 612); 3,000 tokens, 16/16 heads: 211 -> 179 us.
 #include "common.hpp"
 #include "device.hpp"
 #include "ktiles.hpp"
@@ -48,29 +56,36 @@ namespace bdlm {
 
 namespace {
 
-constexpr int kD = 128;                 // head_dim
-constexpr int kKS = kD / 16;            // k-steps of 16 in a score product
-constexpr int kDT = kD / 32;            // 32-wide d tiles of dK^T / dV^T
-constexpr int kBM = 32;                 // query rows per step
-constexpr int kNH = 2;                  // query heads per step
+constexpr int kSub = 32;     // query rows of a sub-block: a step is two of them
 constexpr int kStages = 4;
-constexpr uint32_t kRB = kD * 2;        // bytes per row
-constexpr uint32_t kHB = kBM * kRB;     // bytes per head in a stage tile (8 KB)
-constexpr uint32_t kTileB = kNH * kHB;  // Q (or dO) tile of a stage (16 KB)
-// LDS: the four Q tiles, then the four dO tiles (each region 64 KB, so every
-// read address is a per-lane register plus an immediate offset below 2^16),
-// then per stage -LSE/scale and -D of the step's 2 x 32 rows.
-constexpr uint32_t kQRegion = 0;
-constexpr uint32_t kDoRegion = kStages * kTileB;                 // 65536
-constexpr uint32_t kStatRegion = 2 * kStages * kTileB;           // 131072
-constexpr uint32_t kStatB = 2 * kNH * kBM * 4;                   // 512 bytes per stage
-constexpr uint32_t kSpareRegion = kStatRegion + kStages * kStatB; // empty copies of waves 0, 1
-constexpr uint32_t kLdsBytes = kSpareRegion + 2 * 256;             // 133632
-// Copy plan: a tensor tile of a step is 2 heads x 32 rows x 16 chunks = 1024
-// 16-byte slots = 16 instructions of 64 lanes; waves 0-1 copy Q, waves 2-3 dO,
-// 8 instructions each; one more dword instruction per wave copies the 64
-// floats of -LSE/scale (wave 2) or -D (wave 3) (waves 0, 1: an empty copy).
-constexpr int kIPW = 8;
+
+// Shapes of one instantiation.  D: head_dim.  ROWS false: the two sub-blocks
+// of a step are the same 32 rows of two query heads (even GQA groups); true:
+// 64 consecutive rows of one head (odd groups).
+template <int D, bool ROWS>
+struct Shape {
+  static constexpr int KS = D / 16;               // k-steps of 16 in a score product
+  static constexpr int DT = D / 32;               // 32-wide d tiles of dK^T / dV^T
+  static constexpr int BM = ROWS ? 2 * kSub : kSub;  // query rows per step
+  static constexpr int HPS = ROWS ? 1 : 2;        // query heads per step
+  static constexpr uint32_t RB = D * 2;           // bytes per row
+  static constexpr uint32_t HB = kSub * RB;       // bytes per sub-block in a stage tile (8 KB at D = 128)
+  static constexpr uint32_t TileB = 2 * HB;       // Q (or dO) tile of a stage (16 KB)
+  // LDS: the four Q tiles, then the four dO tiles (each region 64 KB at D =
+  // 128, so every read address is a per-lane register plus an immediate offset
+  // below 2^16), then per stage -LSE/scale and -D of the step's 2 x 32 rows.
+  static constexpr uint32_t QRegion = 0;
+  static constexpr uint32_t DoRegion = kStages * TileB;
+  static constexpr uint32_t StatRegion = 2 * kStages * TileB;
+  static constexpr uint32_t StatB = 2 * 2 * kSub * 4;                   // 512 bytes per stage
+  static constexpr uint32_t SpareRegion = StatRegion + kStages * StatB;  // empty copies of waves 0, 1
+  static constexpr uint32_t LdsBytes = SpareRegion + 2 * 256;            // 133632 at D = 128, 68096 at D = 64
+  // Copy plan: a tensor tile of a step is 64 rows x D / 8 16-byte slots;
+  // waves 0-1 copy Q, waves 2-3 dO, IPW instructions of 64 lanes each; one
+  // more dword instruction per wave copies the 64 floats of -LSE/scale (wave
+  // 2) or -D (wave 3) (waves 0, 1: an empty copy).
+  static constexpr int IPW = 64 * (D / 8) / 64 / 2;
+};
 
 __device__ __forceinline__ void mfma_agpr(f32x16& acc, const bf16x8& a, const bf16x8& b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
@@ -108,9 +123,9 @@ __device__ __forceinline__ f32x4 lds_f4(uint32_t a) {
   return *(__attribute__((address_space(3))) const f32x4*)(uintptr_t)a;
 }
 
-// Descriptors of step i of a key tile's walk (walk_step): its 32-row block,
+// Descriptors of step i of a key tile's walk (walk_step): its row block,
 // q | partial << 1, and words 0-2 of the buffer resources of its tensor rows
-// (32 rows x 2 heads from block s of range q, head pair hp) and of its
+// (BM rows x HPS heads from block s of range q, head group hp) and of its
 // statistics row; steps past the end copy nothing and are not partial.  Plain
 // scalar parameters: as a lambda over captured variables, the compiler turned
 // the per-lane selects into indexed loads from a stack copy of the captures.
@@ -118,11 +133,12 @@ struct StepDesc {
   int s, flags;
   uint32_t t0, t1, t2, l0, l1, l2;
 };
+template <int D, bool ROWS>
 __device__ __forceinline__ StepDesc step_desc(const WalkPlan& wp, int i, int64_t H, bool stats_wave, int len_0,
                                               int len_1, int f0_0, int f0_1, int f1_0, int f1_1, uint32_t lrec_0,
                                               uint32_t lrec_1, uint64_t tb_0, uint64_t tb_1, uint64_t lb_0,
                                               uint64_t lb_1) {
-  constexpr int BM = kBM, NH = kNH;
+  constexpr int BM = Shape<D, ROWS>::BM, NH = Shape<D, ROWS>::HPS;
   const WalkStep ws = walk_step(wp, i);
   const bool live = ws.live;
   const int q = live ? ws.q : 0;
@@ -135,10 +151,10 @@ __device__ __forceinline__ StepDesc step_desc(const WalkPlan& wp, int i, int64_t
   d.s = blk;
   const bool part = live && !(blk >= (q ? f0_1 : f0_0) && blk < (q ? f1_1 : f1_0));
   d.flags = q | (part ? 2 : 0);
-  const uint64_t tp = (q ? tb_1 : tb_0) + (uint64_t)(((int64_t)row0 * H + hoff) * kD * 2);
+  const uint64_t tp = (q ? tb_1 : tb_0) + (uint64_t)(((int64_t)row0 * H + hoff) * D * 2);
   d.t0 = (uint32_t)tp;
   d.t1 = (uint32_t)(tp >> 32) & 0xffffu;
-  d.t2 = live ? (uint32_t)((nrows - 1) * (int)H + NH) * kD * 2 : 0u;
+  d.t2 = live ? (uint32_t)((nrows - 1) * (int)H + NH) * D * 2 : 0u;
   const int loff = live ? hoff * len + row0 : 0;
   const uint64_t lp = (q ? lb_1 : lb_0) + (uint64_t)loff * 4u;
   d.l0 = (uint32_t)lp;
@@ -151,11 +167,13 @@ __device__ __forceinline__ StepDesc step_desc(const WalkPlan& wp, int i, int64_t
 // 16-row half as second bf16 terms when some probability of that half reaches
 // hilo_tau (8 more products: head 0's after block B, head 1's after block D,
 // each while its P and dS are still in registers).
-template <bool ADAPT>
+template <int D, bool ADAPT, bool ROWS>
 __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
-  constexpr int BN = kBwdKeysBf16, BM = kBM, NH = kNH;
+  using Sh = Shape<D, ROWS>;
+  constexpr int BN = kBwdKeysBf16, BM = Sh::BM, HPS = Sh::HPS, KS = Sh::KS, DT = Sh::DT, IPW = Sh::IPW;
+  constexpr uint32_t RB = Sh::RB, HB = Sh::HB, TileB = Sh::TileB;
   static_assert(BN == 128, "tile shape");
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[kLdsBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[Sh::LdsBytes];
   const uint32_t L0 = lds_addr(lds);
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -178,23 +196,23 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   const int kpos_first = kr.pos0 + key0, kpos_last = kr.pos0 + key0 + nk - 1;
 
   // ---- K, V rows of this wave's keys (B operands of the score products), in AGPRs
-  bf16x8 kf[kKS], vf[kKS];
+  bf16x8 kf[KS], vf[KS];
   {
-    const int64_t eoff = (((int64_t)b * kr.bstride + key0) * HKV + kvh) * kD;
-    const uint32_t bytes = (uint32_t)(((int64_t)(nk - 1) * HKV * kD + kD) * 2);
+    const int64_t eoff = (((int64_t)b * kr.bstride + key0) * HKV + kvh) * D;
+    const uint32_t bytes = (uint32_t)(((int64_t)(nk - 1) * HKV * D + D) * 2);
     const auto rk = make_rsrc((const bf16*)kr.k + eoff, bytes);
     const auto rv = make_rsrc((const bf16*)kr.v + eoff, bytes);
-    const uint32_t off = (uint32_t)(((int64_t)mykey * HKV * kD + 8 * half) * 2);
+    const uint32_t off = (uint32_t)(((int64_t)mykey * HKV * D + 8 * half) * 2);
 #pragma unroll
-    for (int s = 0; s < kKS; ++s) {
+    for (int s = 0; s < KS; ++s) {
       kf[s] = __builtin_bit_cast(bf16x8, buf_load16(rk, off + 32 * s));
       vf[s] = __builtin_bit_cast(bf16x8, buf_load16(rv, off + 32 * s));
     }
   }
   // dK^T / dV^T accumulators (AGPRs, written only by the inline-assembly MFMAs)
-  f32x16 dka[kDT], dva[kDT];
+  f32x16 dka[DT], dva[DT];
 #pragma unroll
-  for (int d = 0; d < kDT; ++d) {
+  for (int d = 0; d < DT; ++d) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       dka[d][i] = 0.f;
@@ -219,7 +237,7 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
     sp.pos0 = qr.pos0;
     sp.len = qr.len;
     const int h0 = kvh * a.group;
-    sp.tb = (const bf16*)(w < 2 ? qr.q : qr.dO) + ((int64_t)b * qr.bstride * H + h0) * kD;
+    sp.tb = (const bf16*)(w < 2 ? qr.q : qr.dO) + ((int64_t)b * qr.bstride * H + h0) * D;
     const int64_t lrow = ((int64_t)b * H + h0) * qr.len;
     sp.lb = (w == 2 ? qr.l2 : qr.delta) + lrow;
     sp.lrec = (uint32_t)(((int64_t)a.batch * H * qr.len - lrow) * 4);
@@ -248,7 +266,7 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   auto sel2 = [](int q, auto v0, auto v1) { return q ? v1 : v0; };
 #define BDLM_PICK(f, q) sel2((q), R0.f, R1.f)
   // The walk by step index (walk_plan, walk_step).
-  WalkPlan wp = walk_plan(R0.s0, R0.s1, R1.s0, R1.s1, a.group / NH);
+  WalkPlan wp = walk_plan(R0.s0, R0.s1, R1.s0, R1.s1, a.group / HPS);
   // This workgroup's chunk of it: steps [n0, n1).
   const int max_ch = a.split.chunks[r];
   const int nch = max_ch > 1 ? chunks_of(wp.nsteps, a.split.unit, max_ch) : 1;
@@ -257,21 +275,21 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   const int n0 = it.chunk * a.split.unit, n1 = it.chunk + 1 < nch ? n0 + a.split.unit : wp.nsteps;
   wp.nsteps = n1;  // (steps past the chunk copy nothing)
 
-  // ---- copies.  Instruction i of a wave is instruction (w & 1) * kIPW + i of
+  // ---- copies.  Instruction i of a wave is instruction (w & 1) * IPW + i of
   // its tensor; the per-lane global offsets are constant over the walk.
   const int wodd = w & 1;
-  uint32_t voff[kIPW];
+  uint32_t voff[IPW];
 #pragma unroll
-  for (int i = 0; i < kIPW; ++i) {
-    const int slot = (wodd * kIPW + i) * 64 + lane;
-    const int row = slot / 16, ch = (slot % 16) ^ chunk_swz<kD>(row);
-    const int j = row / BM, rr = row % BM;
-    voff[i] = (uint32_t)(((rr * H + j) * kD + ch * 8) * 2);
+  for (int i = 0; i < IPW; ++i) {
+    const int slot = (wodd * IPW + i) * 64 + lane;
+    const int row = slot / (D / 8), ch = (slot % (D / 8)) ^ chunk_swz<D>(row);
+    const int head = ROWS ? 0 : row / kSub, rr = ROWS ? row : row % kSub;
+    voff[i] = (uint32_t)(((rr * H + head) * D + ch * 8) * 2);
   }
-  // A step's copies: kIPW 16-byte instructions of the wave's tensor and one
+  // A step's copies: IPW 16-byte instructions of the wave's tensor and one
   // dword instruction of -LSE/scale (wave 2) or -D (wave 3); waves 0 and 1
   // issue an empty dword copy into a spare LDS row instead, so that every wave
-  // has kIPW + 1 copies per step in flight.
+  // has IPW + 1 copies per step in flight.
   struct CopyPlan {
     u32x4 rt, rl;   // resources: the wave's tensor rows, its -LSE/scale or -D row
     uint32_t lvo;   // per-lane offset of the dword copy
@@ -285,14 +303,14 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   const uint64_t tb_0 = (uint64_t)(uintptr_t)R0.tb, tb_1 = (uint64_t)(uintptr_t)R1.tb;
   const uint64_t lb_0 = (uint64_t)(uintptr_t)R0.lb, lb_1 = (uint64_t)(uintptr_t)R1.lb;
   auto make_batch = [&](int base) __attribute__((always_inline)) -> StepDesc {
-    return step_desc(wp, base + lane, H, w >= 2, len_0, len_1, f0_0, f0_1, f1_0, f1_1, lrec_0, lrec_1, tb_0, tb_1,
+    return step_desc<D, ROWS>(wp, base + lane, H, w >= 2, len_0, len_1, f0_0, f0_1, f1_0, f1_1, lrec_0, lrec_1, tb_0, tb_1,
                      lb_0, lb_1);
   };
   StepDesc bt;
   int bbase = n0;
-  // Per-lane offsets of the dword copy for each range (rows of two heads).
-  const uint32_t lvo0 = (uint32_t)(((lane >> 5) * R0.len + (lane & 31)) * 4);
-  const uint32_t lvo1 = (uint32_t)(((lane >> 5) * R1.len + (lane & 31)) * 4);
+  // Per-lane offsets of the dword copy for each range (32 rows of two heads, or 64 rows of one).
+  const uint32_t lvo0 = (uint32_t)(ROWS ? lane * 4 : ((lane >> 5) * R0.len + (lane & 31)) * 4);
+  const uint32_t lvo1 = (uint32_t)(ROWS ? lane * 4 : ((lane >> 5) * R1.len + (lane & 31)) * 4);
   auto rl = [&](uint32_t v, int i) __attribute__((always_inline)) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, i - bbase);
   };
@@ -311,11 +329,11 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
     return cp;
   };
   auto copy_issue = [&](const CopyPlan& cp, int st, int i) __attribute__((always_inline)) {
-    if (i < kIPW) {
-      dma16(cp.rt, L0 + (w < 2 ? kQRegion : kDoRegion) + st * kTileB + (wodd * kIPW + i) * 1024, voff[i]);
+    if (i < IPW) {
+      dma16(cp.rt, L0 + (w < 2 ? Sh::QRegion : Sh::DoRegion) + st * TileB + (wodd * IPW + i) * 1024, voff[i]);
     } else {
       const uint32_t ldst =
-          w >= 2 ? L0 + kStatRegion + st * kStatB + (w == 2 ? 0u : 256u) : L0 + kSpareRegion + w * 256;
+          w >= 2 ? L0 + Sh::StatRegion + st * Sh::StatB + (w == 2 ? 0u : 256u) : L0 + Sh::SpareRegion + w * 256;
       dma4(cp.rl, ldst, cp.lvo);
     }
   };
@@ -330,7 +348,7 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
     const CopyPlan cp = copy_plan(i);
     plan_ready(cp);
 #pragma unroll
-    for (int i = 0; i <= kIPW; ++i) copy_issue(cp, st, i);
+    for (int i = 0; i <= IPW; ++i) copy_issue(cp, st, i);
   };
 
   const float c = a.scale_log2;
@@ -338,43 +356,60 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   // Row reads: lane (half, l32) reads logical chunk 2k + half of row l32.
   // (The dO addresses are laundered through an empty asm statement: otherwise
   // the compiler re-derives them from the Q addresses with an add per read.)
-  uint32_t yq[kKS], yd[kKS];
+  uint32_t yq[KS], yd[KS];
 #pragma unroll
-  for (int k = 0; k < kKS; ++k) {
-    yq[k] = (L0 + kQRegion + swz_row_part<kD>(l32, half)) ^ (32u * k);
-    yd[k] = yq[k] + kDoRegion;
+  for (int k = 0; k < KS; ++k) {
+    yq[k] = (L0 + Sh::QRegion + swz_row_part<D>(l32, half)) ^ (32u * k);
+    yd[k] = yq[k] + Sh::DoRegion;
     asm volatile("" : "+v"(yd[k]));
   }
   // Transpose reads: rows 16u + R0 and 16u + R0 + 8 of the head's tile, 8-byte
   // piece 8d + 4 (G & 1) + (sl & 3).
-  uint32_t tq0[kDT], tq1[kDT], td0[kDT], td1[kDT];
+  uint32_t tq0[DT], tq1[DT], td0[DT], td1[DT];
 #pragma unroll
-  for (int d = 0; d < kDT; ++d) {
-    tq0[d] = (L0 + kQRegion + swz_tr_part<kD>(G, sl, 0)) ^ (64u * d);
-    tq1[d] = (L0 + kQRegion + swz_tr_part<kD>(G, sl, 8)) ^ (64u * d);
-    td0[d] = tq0[d] + kDoRegion;
-    td1[d] = tq1[d] + kDoRegion;
+  for (int d = 0; d < DT; ++d) {
+    tq0[d] = (L0 + Sh::QRegion + swz_tr_part<D>(G, sl, 0)) ^ (64u * d);
+    tq1[d] = (L0 + Sh::QRegion + swz_tr_part<D>(G, sl, 8)) ^ (64u * d);
+    td0[d] = tq0[d] + Sh::DoRegion;
+    td1[d] = tq1[d] + Sh::DoRegion;
     asm volatile("" : "+v"(td0[d]), "+v"(td1[d]));
   }
   // Accumulator starts of a step: for head j, register i of a lane holds query
   // row 8 (i / 4) + 4 half + i % 4 of the step.
-  uint32_t ystat = L0 + kStatRegion + (uint32_t)(4 * half) * 4;
+  uint32_t ystat = L0 + Sh::StatRegion + (uint32_t)(4 * half) * 4;
   asm volatile("" : "+v"(ystat));  // one base register; stage, head and row offsets stay immediate
 
-  f32x16 sa[NH], da[NH];
+  f32x16 sa[2], da[2];
   // The first row-read pairs of a step, issued at the end of the step before
   // (its stage is complete from the barrier before that step on).
-  constexpr int RA = 4;  // row-read pairs in flight ahead of the score products
+  constexpr int RA = D == 128 ? 4 : ADAPT ? 1 : 2;  // row-read pairs in flight ahead of the score products
   bf16x8 nq[RA], nd[RA];
+  // Starts at -inf where the row mbase + (offset of register i) is hidden from the lane's key.
+  auto mask_sub = [](f32x16& s, int mbase, int lane_qw) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      float x0 = s[i];
+      uint32_t tmp;
+      asm volatile(
+          "v_add_u32 %1, %2, %3\n\t"
+          "v_cmp_lt_u32 vcc, %1, %4\n\t"
+          "v_mov_b32 %1, 0xff800000\n\t"
+          "v_cndmask_b32 %0, %1, %0, vcc"
+          : "+v"(x0), "=&v"(tmp)
+          : "n"(8 * (i >> 2) + (i & 3)), "v"(mbase), "v"(lane_qw)
+          : "vcc");
+      s[i] = x0;
+    }
+  };
   // Load the starts of step i (stage st) and apply the mask of partly visible steps.
   auto load_starts = [&](int st, int si) __attribute__((always_inline)) {
-    const uint32_t base = ystat + st * kStatB;
+    const uint32_t base = ystat + st * Sh::StatB;
 #pragma unroll
-    for (int j = 0; j < NH; ++j)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
-        const f32x4 l = lds_f4(base + (j * BM + 8 * g4) * 4);
-        const f32x4 dd = lds_f4(base + 256 + (j * BM + 8 * g4) * 4);
+        const f32x4 l = lds_f4(base + (j * kSub + 8 * g4) * 4);
+        const f32x4 dd = lds_f4(base + 256 + (j * kSub + 8 * g4) * 4);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           sa[j][4 * g4 + e] = l[e];
@@ -388,22 +423,27 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
     if (fl & 2) {
       const int mbase = BDLM_PICK(pos0, q) + (int)rl((uint32_t)bt.s, si) * BM + 4 * half - BDLM_PICK(qa, q);
       const int lane_qw = BDLM_PICK(qw, q);
+      if constexpr (ROWS) {
+        mask_sub(sa[0], mbase, lane_qw);
+        mask_sub(sa[1], mbase + kSub, lane_qw);
+      } else {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        float x0 = sa[0][i], x1 = sa[1][i];
-        uint32_t tmp;
-        // hidden when (unsigned)(mbase + row offset of register i) >= lane_qw
-        asm volatile(
-            "v_add_u32 %2, %3, %4\n\t"
-            "v_cmp_lt_u32 vcc, %2, %5\n\t"
-            "v_mov_b32 %2, 0xff800000\n\t"
-            "v_cndmask_b32 %0, %2, %0, vcc\n\t"
-            "v_cndmask_b32 %1, %2, %1, vcc"
-            : "+v"(x0), "+v"(x1), "=&v"(tmp)
-            : "n"(8 * (i >> 2) + (i & 3)), "v"(mbase), "v"(lane_qw)
-            : "vcc");
-        sa[0][i] = x0;
-        sa[1][i] = x1;
+        for (int i = 0; i < 16; ++i) {
+          float x0 = sa[0][i], x1 = sa[1][i];
+          uint32_t tmp;
+          // hidden when (unsigned)(mbase + row offset of register i) >= lane_qw
+          asm volatile(
+              "v_add_u32 %2, %3, %4\n\t"
+              "v_cmp_lt_u32 vcc, %2, %5\n\t"
+              "v_mov_b32 %2, 0xff800000\n\t"
+              "v_cndmask_b32 %0, %2, %0, vcc\n\t"
+              "v_cndmask_b32 %1, %2, %1, vcc"
+              : "+v"(x0), "+v"(x1), "=&v"(tmp)
+              : "n"(8 * (i >> 2) + (i & 3)), "v"(mbase), "v"(lane_qw)
+              : "vcc");
+          sa[0][i] = x0;
+          sa[1][i] = x1;
+        }
       }
     }
   };
@@ -411,11 +451,11 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   // The starts of head j of step `cu` (stage st) into s, d, with the mask of
   // partly visible steps (the values load_starts gives that head).
   auto load_head_starts = [&](int st, int si, int j, f32x16& s, f32x16& d) __attribute__((always_inline)) {
-    const uint32_t base = ystat + st * kStatB;
+    const uint32_t base = ystat + st * Sh::StatB;
 #pragma unroll
     for (int g4 = 0; g4 < 4; ++g4) {
-      const f32x4 l = lds_f4(base + (j * BM + 8 * g4) * 4);
-      const f32x4 dd = lds_f4(base + 256 + (j * BM + 8 * g4) * 4);
+      const f32x4 l = lds_f4(base + (j * kSub + 8 * g4) * 4);
+      const f32x4 dd = lds_f4(base + 256 + (j * kSub + 8 * g4) * 4);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         s[4 * g4 + e] = l[e];
@@ -426,37 +466,24 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
     if (fl & 2) {
       const int mbase = BDLM_PICK(pos0, q) + (int)rl((uint32_t)bt.s, si) * BM + 4 * half - BDLM_PICK(qa, q);
       const int lane_qw = BDLM_PICK(qw, q);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        float x0 = s[i];
-        uint32_t tmp;
-        asm volatile(
-            "v_add_u32 %1, %2, %3\n\t"
-            "v_cmp_lt_u32 vcc, %1, %4\n\t"
-            "v_mov_b32 %1, 0xff800000\n\t"
-            "v_cndmask_b32 %0, %1, %0, vcc"
-            : "+v"(x0), "=&v"(tmp)
-            : "n"(8 * (i >> 2) + (i & 3)), "v"(mbase), "v"(lane_qw)
-            : "vcc");
-        s[i] = x0;
-      }
+      mask_sub(s, mbase + (ROWS ? j * kSub : 0), lane_qw);
     }
   };
 
   // One step on stage ST: the copies of step `cp` into stage CP go out under
   // its first products, the starts of step `nx` (stage NX) are loaded under its
   // last ones, and the walk advances under the softmax of head 0.
-  constexpr int TA = 8;  // transpose-read pairs in flight ahead of the dV/dK products
+  constexpr int TA = D == 128 ? 8 : ADAPT ? 2 : 4;  // transpose-read pairs in flight ahead of the dV/dK products
   int i0 = n0;   // the current step
   CopyPlan cpl;  // copies of step i0 + 3, planned during the step before
   auto run_step = [&](auto st_c, auto nx_c, int cp_stage) __attribute__((always_inline)) {
     constexpr int ST = decltype(st_c)::value, NX = decltype(nx_c)::value;
-    constexpr uint32_t SO = ST * kTileB;  // stage offset inside a tensor region
+    constexpr uint32_t SO = ST * TileB;  // stage offset inside a tensor region
     // ---- A and B: S_j = Q_j K^T + start, dP_j = dO_j V^T + start, j = 0, 1 (32
     // products), the softmax of head 0 under the products of head 1.
     bf16x8 rq[RA + 1], rd[RA + 1];
-    auto rowq = [&](int n) { return lds_load16(yq[n % kKS] + SO + (n / kKS) * kHB); };
-    auto rowd = [&](int n) { return lds_load16(yd[n % kKS] + SO + (n / kKS) * kHB); };
+    auto rowq = [&](int n) { return lds_load16(yq[n % KS] + SO + (n / KS) * HB); };
+    auto rowd = [&](int n) { return lds_load16(yd[n % KS] + SO + (n / KS) * HB); };
 #pragma unroll
     for (int n = 0; n < RA; ++n) {
       rq[n] = nq[n];
@@ -464,44 +491,46 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
     }
     // Transpose reads of blocks C and D: rows 16u .. 16u + 15 of head j.
     auto trd = [&](int j, int u, int d) {
-      const uint32_t o = SO + j * kHB + u * 16 * kRB;
+      const uint32_t o = SO + j * HB + u * 16 * RB;
       return cat(lds_read_tr_at(td0[d] + o), lds_read_tr_at(td1[d] + o));
     };
     auto trq = [&](int j, int u, int d) {
-      const uint32_t o = SO + j * kHB + u * 16 * kRB;
+      const uint32_t o = SO + j * HB + u * 16 * RB;
       return cat(lds_read_tr_at(tq0[d] + o), lds_read_tr_at(tq1[d] + o));
     };
-    // product m of a head: m < 8 -> dV (u = m / 4, d = m % 4), else dK
-    auto opnd = [&](int j, int m) { return m < 8 ? trd(j, m / 4, m % 4) : trq(j, (m - 8) / 4, (m - 8) % 4); };
+    // product m of a sub-block: m < MD -> dV (u = m / DT, d = m % DT), else dK
+    constexpr int MD = 2 * DT;
+    auto opnd = [&](int j, int m) { return m < MD ? trd(j, m / DT, m % DT) : trq(j, (m - MD) / DT, (m - MD) % DT); };
     bf16x8 tf[TA + 1];
-    bf16x8 pb[NH][2], dsb[NH][2];
-    float pm[NH][2] = {{0.f, 0.f}, {0.f, 0.f}};  // ADAPT: largest P per head and 16-row half
+    bf16x8 pb[2][2], dsb[2][2];
+    float pm[2][2] = {{0.f, 0.f}, {0.f, 0.f}};  // ADAPT: largest P per head and 16-row half
 #pragma unroll
-    for (int n = 0; n < 2 * kKS; ++n) {
-      if (n + RA < 2 * kKS) {
+    for (int n = 0; n < 2 * KS; ++n) {
+      if (n + RA < 2 * KS) {
         rq[(n + RA) % (RA + 1)] = rowq(n + RA);
         rd[(n + RA) % (RA + 1)] = rowd(n + RA);
       }
-      if (n >= 2 * kKS - TA) tf[n - (2 * kKS - TA)] = opnd(0, n - (2 * kKS - TA));  // block C's first operands
-      const int j = n / kKS, k = n % kKS;
+      if (n >= 2 * KS - TA) tf[n - (2 * KS - TA)] = opnd(0, n - (2 * KS - TA));  // block C's first operands
+      const int j = n / KS, k = n % KS;
       sa[j] = mfma32(rq[n % (RA + 1)], kf[k], sa[j]);
       da[j] = mfma32(rd[n % (RA + 1)], vf[k], da[j]);
-      if (n <= kIPW) copy_issue(cpl, cp_stage, n);
-      if (n == kIPW + 3) cpl = copy_plan(i0 + 4);
-      if (n == kIPW + 4) plan_ready(cpl);
+      if (n <= IPW) copy_issue(cpl, cp_stage, n);
+      if (n == IPW + (D == 128 ? 3 : 1)) cpl = copy_plan(i0 + 4);
+      if (n == IPW + (D == 128 ? 4 : 2)) plan_ready(cpl);
 
       if (j == 1) {
-        // softmax of head 0: two scores per product pair
+        // softmax of sub-block 0: SPP scores per product pair
+        constexpr int SPP = 16 / KS;
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int i = 2 * k + e;
+        for (int e = 0; e < SPP; ++e) {
+          const int i = SPP * k + e;
           const float p = exp2f_fast(sa[0][i] * c);
           da[0][i] = p * da[0][i];
           sa[0][i] = p;
           if constexpr (ADAPT) pm[0][i >> 3] = fmaxf(pm[0][i >> 3], p);
         }
-        if (k & 1) {
-          const int i0 = 2 * (k - 1);
+        if ((SPP * (k + 1)) % 4 == 0) {
+          const int i0 = SPP * (k + 1) - 4;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             pb[0][(i0 + e) >> 3][(i0 + e) & 7] = to_bf16(sa[0][i0 + e]);
@@ -525,11 +554,11 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
           // All eight operands are read before the residuals are formed, whose
           // vector work covers the reads' latency (8K, 32/4 heads: the kernel
           // 3.36 -> 3.14 ms against reading each before its product).
-          bf16x8 od[kDT], oq[kDT];
+          bf16x8 od[DT], oq[DT];
 #pragma unroll
-          for (int d = 0; d < kDT; ++d) od[d] = trd(j, u, d);
+          for (int d = 0; d < DT; ++d) od[d] = trd(j, u, d);
 #pragma unroll
-          for (int d = 0; d < kDT; ++d) oq[d] = trq(j, u, d);
+          for (int d = 0; d < DT; ++d) oq[d] = trq(j, u, d);
           fence();
           bf16x8 pl, dl;
 #pragma unroll
@@ -539,9 +568,9 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
             dl[e] = to_bf16(ds - (float)to_bf16(ds));
           }
 #pragma unroll
-          for (int d = 0; d < kDT; ++d) mfma_agpr_padded(dva[d], od[d], pl);
+          for (int d = 0; d < DT; ++d) mfma_agpr_padded(dva[d], od[d], pl);
 #pragma unroll
-          for (int d = 0; d < kDT; ++d) mfma_agpr_padded(dka[d], oq[d], dl);
+          for (int d = 0; d < DT; ++d) mfma_agpr_padded(dka[d], oq[d], dl);
         }
       }
     };
@@ -550,32 +579,38 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
       fence();
     }
 #pragma unroll
-    for (int n = 0; n < 32; ++n) {
-      if (n + TA < 32) tf[(n + TA) % (TA + 1)] = opnd((n + TA) / 16, (n + TA) % 16);
-      const int j = n / 16, m = n % 16;
-      if (m < 8) mfma_agpr(dva[m % 4], tf[n % (TA + 1)], pb[j][m / 4]);
-      else mfma_agpr(dka[(m - 8) % 4], tf[n % (TA + 1)], dsb[j][(m - 8) / 4]);
+    for (int n = 0; n < 4 * MD; ++n) {
+      if (n + TA < 4 * MD) tf[(n + TA) % (TA + 1)] = opnd((n + TA) / (2 * MD), (n + TA) % (2 * MD));
+      const int j = n / (2 * MD), m = n % (2 * MD);
+      if (m < MD) mfma_agpr(dva[m % DT], tf[n % (TA + 1)], pb[j][m / DT]);
+      else mfma_agpr(dka[(m - MD) % DT], tf[n % (TA + 1)], dsb[j][(m - MD) / DT]);
       if (j == 0) {
-        // P_1 = exp2(c S_1): one score per product
-        sa[1][m] = exp2f_fast(sa[1][m] * c);
-        if constexpr (ADAPT) pm[1][m >> 3] = fmaxf(pm[1][m >> 3], sa[1][m]);
-        if (m & 1) {
-          pb[1][m >> 3][(m - 1) & 7] = to_bf16(sa[1][m - 1]);
-          pb[1][m >> 3][m & 7] = to_bf16(sa[1][m]);
-        }
-      } else if (m < 8) {
-        // dS_1 = P_1 dP_1 under the dV products of head 1
+        // P_1 = exp2(c S_1): SP scores per product
+        constexpr int SP = 16 / (2 * MD);
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int i = 2 * m + e;
+        for (int e = 0; e < SP; ++e) {
+          const int i = SP * m + e;
+          sa[1][i] = exp2f_fast(sa[1][i] * c);
+          if constexpr (ADAPT) pm[1][i >> 3] = fmaxf(pm[1][i >> 3], sa[1][i]);
+          if (i & 1) {
+            pb[1][i >> 3][(i - 1) & 7] = to_bf16(sa[1][i - 1]);
+            pb[1][i >> 3][i & 7] = to_bf16(sa[1][i]);
+          }
+        }
+      } else if (m < MD) {
+        // dS_1 = P_1 dP_1 under the dV products of sub-block 1
+        constexpr int SD = 16 / MD;
+#pragma unroll
+        for (int e = 0; e < SD; ++e) {
+          const int i = SD * m + e;
           da[1][i] = sa[1][i] * da[1][i];
         }
-        if (m & 1) {
-          const int i0 = 2 * (m - 1);
+        if ((SD * (m + 1)) % 4 == 0) {
+          const int i0 = SD * (m + 1) - 4;
 #pragma unroll
           for (int e = 0; e < 4; ++e) dsb[1][(i0 + e) >> 3][(i0 + e) & 7] = to_bf16(da[1][i0 + e]);
         }
-      } else if (m == 8) {
+      } else if (m == MD) {
         if constexpr (!ADAPT) load_starts(NX, i0 + 1);
         else load_head_starts(NX, i0 + 1, 0, sa[0], da[0]);
       }
@@ -590,10 +625,10 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
     }
 #pragma unroll
     for (int i = 0; i < RA; ++i) {
-      nq[i] = lds_load16(yq[i] + NX * kTileB);
-      nd[i] = lds_load16(yd[i] + NX * kTileB);
+      nq[i] = lds_load16(yq[i] + NX * TileB);
+      nd[i] = lds_load16(yd[i] + NX * TileB);
     }
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kIPW + 1) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(IPW + 1) : "memory");
     ++i0;
   };
 
@@ -609,12 +644,12 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   copy_step(0, n0);
   copy_step(1, n0 + 1);
   copy_step(2, n0 + 2);
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kIPW + 1) : "memory");  // steps 0 and 1 landed
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(IPW + 1) : "memory");  // steps 0 and 1 landed
   // K and V are pinned in AGPRs only now: pinning reads them, so their loads
   // (issued first) are waited for here, after the walk set-up and the first
   // copies, instead of before them.
 #pragma unroll
-  for (int s = 0; s < kKS; ++s) asm volatile("" : "+a"(kf[s]), "+a"(vf[s]));
+  for (int s = 0; s < KS; ++s) asm volatile("" : "+a"(kf[s]), "+a"(vf[s]));
   load_starts(0, n0);
 #pragma unroll
   for (int i = 0; i < RA; ++i) {
@@ -646,12 +681,12 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
 
   // ---- epilogue: dK = scale dK^T^T, dV (bf16 or fp32); unseen keys get zeros
 #pragma unroll
-  for (int d = 0; d < kDT; ++d) asm volatile("" : "+a"(dka[d]), "+a"(dva[d]));
+  for (int d = 0; d < DT; ++d) asm volatile("" : "+a"(dka[d]), "+a"(dva[d]));
   if (nch > 1) {
     // The chunk's partial sums, in register order (whole cache lines per store).
-    f32x4* pp = (f32x4*)a.split.partials + ((it.slot + it.chunk) * 4 + w) * (2 * kDT * 4 * 64) + lane;
+    f32x4* pp = (f32x4*)a.split.partials + ((it.slot + it.chunk) * 4 + w) * (2 * DT * 4 * 64) + lane;
 #pragma unroll
-    for (int d = 0; d < kDT; ++d)
+    for (int d = 0; d < DT; ++d)
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
         f32x4 vk, vv;
@@ -661,15 +696,15 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
           vv[e] = dva[d][4 * g4 + e];
         }
         pp[(4 * d + g4) * 64] = vk;
-        pp[(4 * kDT + 4 * d + g4) * 64] = vv;
+        pp[(4 * DT + 4 * d + g4) * 64] = vv;
       }
   } else if (a.out_f32) {
     if (key_ok) {
-      const int64_t off = (((int64_t)b * kr.bstride + key0 + mykey) * HKV + kvh) * kD;
+      const int64_t off = (((int64_t)b * kr.bstride + key0 + mykey) * HKV + kvh) * D;
       float* dkp = (float*)kr.dk + off;
       float* dvp = (float*)kr.dv + off;
 #pragma unroll
-      for (int d = 0; d < kDT; ++d)
+      for (int d = 0; d < DT; ++d)
 #pragma unroll
         for (int g4 = 0; g4 < 4; ++g4) {
           f32x4 vk, vv;
@@ -688,9 +723,10 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
     // writes 4 whole rows instead of 16 bytes of each of 32 rows.  Chunk c
     // (16 bytes) of row r sits at chunk c ^ (r & 15): conflict-free reads.
     asm volatile("s_barrier" ::: "memory");
-    const uint32_t sw = L0 + kQRegion + (uint32_t)w * 16384u;
+    const uint32_t sw = L0 + Sh::QRegion + (uint32_t)w * (2 * HB);
+    constexpr int CH = D / 8;  // 16-byte chunks per row
 #pragma unroll
-    for (int d = 0; d < kDT; ++d)
+    for (int d = 0; d < DT; ++d)
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
         bf16x4 vk, vv;
@@ -699,17 +735,17 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
           vk[e] = to_bf16(dka[d][4 * g4 + e] * a.scale);
           vv[e] = to_bf16(dva[d][4 * g4 + e]);
         }
-        const uint32_t o = (uint32_t)l32 * 256u + (((uint32_t)(4 * d + g4) ^ (uint32_t)(l32 & 15)) * 16u) + 8u * half;
+        const uint32_t o = (uint32_t)l32 * RB + (((uint32_t)(4 * d + g4) ^ (uint32_t)(l32 & (CH - 1))) * 16u) + 8u * half;
         lds_store8(sw + o, vk);
-        lds_store8(sw + 8192u + o, vv);
+        lds_store8(sw + HB + o, vv);
       }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int r = i * 4 + (lane >> 4), c = lane & 15;
-      const uint32_t o = (uint32_t)r * 256u + (((uint32_t)c ^ (uint32_t)(r & 15)) * 16u);
-      const bf16x8 xk = lds_load16(sw + o), xv = lds_load16(sw + 8192u + o);
+    for (int i = 0; i < CH / 2; ++i) {
+      const int r = i * (64 / CH) + lane / CH, c = lane % CH;
+      const uint32_t o = (uint32_t)r * RB + (((uint32_t)c ^ (uint32_t)(r & (CH - 1))) * 16u);
+      const bf16x8 xk = lds_load16(sw + o), xv = lds_load16(sw + HB + o);
       if (w * 32 + r < nk) {
-        const int64_t go = (((int64_t)b * kr.bstride + key0 + w * 32 + r) * HKV + kvh) * kD + c * 8;
+        const int64_t go = (((int64_t)b * kr.bstride + key0 + w * 32 + r) * HKV + kvh) * D + c * 8;
         *(bf16x8*)((bf16*)kr.dk + go) = xk;
         *(bf16x8*)((bf16*)kr.dv + go) = xv;
       }
@@ -721,28 +757,30 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
 // order.  A thread owns 8 consecutive head_dim elements of one key of dK or
 // dV, two 16-byte pieces of each partial; kSumWgs workgroups per tile.  HBM
 // (mostly L2 and MALL) traffic: the partials once.
-constexpr int kSumWgs = 4 * 2 * kDT * 4 * 32 / 256;
+template <int D>
+constexpr int kSumWgs = 4 * 2 * D / 32 * 4 * 32 / 256;
+template <int D>
 __global__ __launch_bounds__(256) void dkdv_sum_kernel(const AttnArgs a) {
+  constexpr int DT = D / 32, PIECES = 2 * DT * 4;  // per 32 keys: dK's 4 d + g4, then dV's
   SumItem it;
-  sum_item(a, blockIdx.x / kSumWgs, it);
+  sum_item(a, blockIdx.x / kSumWgs<D>, it);
   const int nch = a.split.counts[it.slot];
   if (nch <= 1) return;
-  const int n = (blockIdx.x % kSumWgs) * 256 + threadIdx.x;
-  const int l32 = n & 31, piece = (n >> 5) & (2 * kDT * 4 - 1), w = n >> 10;  // piece: dK's 4 d + g4, then dV's
-  static_assert(2 * kDT * 4 == 32, "index split");
-  const f32x4* pp = (const f32x4*)a.split.partials + (it.slot * 4 + w) * (2 * kDT * 4 * 64) + piece * 64 + l32;
+  const int n = (blockIdx.x % kSumWgs<D>) * 256 + threadIdx.x;
+  const int l32 = n & 31, piece = (n >> 5) % PIECES, w = (n >> 5) / PIECES;
+  const f32x4* pp = (const f32x4*)a.split.partials + (it.slot * 4 + w) * (PIECES * 64) + piece * 64 + l32;
   f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
   for (int ch = 0; ch < nch; ++ch) {
     lo += pp[0];
     hi += pp[32];
-    pp += 4 * 2 * kDT * 4 * 64;
+    pp += 4 * PIECES * 64;
   }
   const KRangeArg& kr = a.kr[it.r];
   const int key = it.t * kBwdKeysBf16 + w * 32 + l32;
   if (key >= kr.len) return;
-  const bool is_dv = piece >= 4 * kDT;
+  const bool is_dv = piece >= 4 * DT;
   const float sc = is_dv ? 1.f : a.scale;
-  const int64_t off = (((int64_t)it.b * kr.bstride + key) * a.kv_heads + it.kvh) * kD + (piece & (4 * kDT - 1)) * 8;
+  const int64_t off = (((int64_t)it.b * kr.bstride + key) * a.kv_heads + it.kvh) * D + (piece & (4 * DT - 1)) * 8;
   void* out = is_dv ? kr.dv : kr.dk;
   if (a.out_f32) {
     *(f32x4*)((float*)out + off) = lo * sc;
@@ -760,21 +798,32 @@ __global__ __launch_bounds__(256) void dkdv_sum_kernel(const AttnArgs a) {
 
 }  // namespace
 
-hipError_t launch_bwd_dkdv_sum(const AttnArgs& a, hipStream_t s) {
-  const int n = a.split.tiles_per_pair * a.kv_heads * a.batch * kSumWgs;
+hipError_t launch_bwd_dkdv_sum(const AttnArgs& a, int head_dim, hipStream_t s) {
+  const int n = a.split.tiles_per_pair * a.kv_heads * a.batch;
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(dkdv_sum_kernel, dim3(n), dim3(256), 0, s, a);
+  if (head_dim == 128) hipLaunchKernelGGL(dkdv_sum_kernel<128>, dim3(n * kSumWgs<128>), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(dkdv_sum_kernel<64>, dim3(n * kSumWgs<64>), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_dkdv(const AttnArgs& a, hipStream_t s) {
+namespace {
+
+template <int D, bool ADAPT>
+void launch_rows(const AttnArgs& a, int n, hipStream_t s) {
+  if (a.group % 2 == 0) hipLaunchKernelGGL((dkdv_kernel<D, ADAPT, false>), dim3(n), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((dkdv_kernel<D, ADAPT, true>), dim3(n), dim3(256), 0, s, a);
+}
+
+}  // namespace
+
+hipError_t launch_bwd_dkdv(const AttnArgs& a, int head_dim, hipStream_t s) {
   const int n = workgroups_for(a.split.wgs_per_pair * a.kv_heads * a.batch);
   if (n == 0) return hipSuccess;
-  // two query heads per step, at most two query ranges (the walk state stays in registers)
-  if (a.group % 2 != 0 || a.n_q > 2) return hipErrorInvalidValue;
-  if (!(a.hilo & kHiloDkDv)) hipLaunchKernelGGL(dkdv_kernel<false>, dim3(n), dim3(256), 0, s, a);
-  else if (a.hilo & kHiloAdaptive) hipLaunchKernelGGL(dkdv_kernel<true>, dim3(n), dim3(256), 0, s, a);
-  else return hipErrorInvalidValue;
+  // at most two query ranges (the walk state stays in registers), no two-term products on every step
+  const bool two_terms = a.hilo & kHiloDkDv;
+  if (a.n_q > 2 || (two_terms && !(a.hilo & kHiloAdaptive))) return hipErrorInvalidValue;
+  if (head_dim == 128) two_terms ? launch_rows<128, true>(a, n, s) : launch_rows<128, false>(a, n, s);
+  else two_terms ? launch_rows<64, true>(a, n, s) : launch_rows<64, false>(a, n, s);
   return hipGetLastError();
 }
 

@@ -243,8 +243,8 @@ hipError_t launch_fwd_bf16(const AttnArgs& a, int head_dim, int rows, hipStream_
 hipError_t launch_fwd_f32(const AttnArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_merge(const MergeArgs& a, int head_dim, int part_dtype, int out_dtype, hipStream_t s);
 hipError_t launch_bwd_bf16(const AttnArgs& a, int head_dim, hipStream_t s);
-hipError_t launch_bwd_dkdv(const AttnArgs& a, hipStream_t s);
-hipError_t launch_bwd_dkdv_sum(const AttnArgs& a, hipStream_t s);
+hipError_t launch_bwd_dkdv(const AttnArgs& a, int head_dim, hipStream_t s);
+hipError_t launch_bwd_dkdv_sum(const AttnArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_bwd_dq_bf16(const AttnArgs& a, int head_dim, int rows, hipStream_t s);
 hipError_t launch_bwd_dq_f32(const AttnArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_bwd_dkv_f32(const AttnArgs& a, int head_dim, hipStream_t s);
@@ -300,10 +300,14 @@ struct WalkStep {
 };
 __host__ __device__ inline WalkStep walk_step(const WalkPlan& w, int i) {
   const bool k1 = i >= w.st1, k2 = i >= w.st2;
-  const int top = (k2 ? w.p2 : k1 ? w.p1 : w.p0) - 1;
-  const int cnt = k2 ? w.cnt2 : k1 ? w.cnt1 : w.cnt0;
-  const int q0 = k2 ? w.q02 : k1 ? w.q01 : w.q00;
-  const int off = i - (k2 ? w.st2 : k1 ? w.st1 : 0);
+  // (selects between differences: selects between fields become loads through
+  // a selected address, which keeps the plan in memory)
+  const int p01 = w.p1 - w.p0, p12 = w.p2 - w.p1, c01 = w.cnt1 - w.cnt0, c12 = w.cnt2 - w.cnt1;
+  const int q01 = w.q01 - w.q00, q12 = w.q02 - w.q01, s12 = w.st2 - w.st1;
+  const int top = w.p0 + (k1 ? p01 : 0) + (k2 ? p12 : 0) - 1;
+  const int cnt = w.cnt0 + (k1 ? c01 : 0) + (k2 ? c12 : 0);
+  const int q0 = w.q00 + (k1 ? q01 : 0) + (k2 ? q12 : 0);
+  const int off = i - (k1 ? w.st1 : 0) - (k2 ? s12 : 0);
   const int per = imax(cnt * w.npairs, 1);
   const int sr = off / per, rem = off - sr * per;
   const int ridx = rem >= w.npairs ? 1 : 0;
@@ -315,14 +319,14 @@ __host__ __device__ inline WalkStep walk_step(const WalkPlan& w, int i) {
   return st;
 }
 
-// The dK/dV kernel of bwd_dkdv.hip (head_dim 128, single-term or adaptive
-// two-term dK/dV products, an even GQA group, at most two query ranges with
-// rows) starts its score and dP accumulators at -LSE/scale and -D, so the backward
-// workspace holds those (stats form 1); the general kernel of bwd_bf16.hip and
-// the fp32 kernel read LSE log2(e) and D (form 0).
-inline bool dkdv_uses_scheduled_kernel(int dtype_bf16, int head_dim, int hilo, int group, int n_q) {
+// The dK/dV kernel of bwd_dkdv.hip (single-term or adaptive two-term dK/dV
+// products, at most two query ranges with rows) starts its score and dP
+// accumulators at -LSE/scale and -D, so the backward workspace holds those
+// (stats form 1); the general kernel of bwd_bf16.hip and the fp32 kernel read
+// LSE log2(e) and D (form 0).
+inline bool dkdv_uses_scheduled_kernel(int dtype_bf16, int hilo, int n_q) {
   const bool terms_ok = !(hilo & kHiloDkDv) || (hilo & kHiloAdaptive);
-  return dtype_bf16 && head_dim == 128 && terms_ok && group % 2 == 0 && n_q <= 2;
+  return dtype_bf16 && terms_ok && n_q <= 2;
 }
 
 // Tile heights the launchers use (the C ABI fills ntiles/tile0 with them).
