@@ -378,7 +378,9 @@ bdlm_status bdlm_attn_fwd(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
     a.kr[j].k = k[j];
     a.kr[j].v = v[j];
   }
-  const int rows = p->dtype == BDLM_BF16 ? bf16_query_rows(p, n_k, k_ranges, kFwdShortWalk) : kRowsF32;
+  const int rows = p->dtype == BDLM_F32              ? kRowsF32
+                   : fwd_short_always(p->head_dim, p->hilo) ? kQRowsShortBf16
+                                                            : bf16_query_rows(p, n_k, k_ranges, kFwdShortWalk);
   const int64_t tiles = tile_ranges(a.qr, n_q, rows);
   if ((st = check_grid(tiles, (int64_t)p->heads * p->batch)) != BDLM_OK) return st;
   a.total_tiles = (int32_t)tiles;

@@ -35,9 +35,18 @@ namespace {
 constexpr float kLn2 = 0.69314718055994530942f;
 constexpr float kSumLimit = 18446744073709551616.f;  // 2^64: a lane's tile sum of p above which m_run moves
 
+// Waves per SIMD: two (the registers and LDS of head_dim 128, and of 8-wave
+// workgroups); three with 4-wave workgroups at head_dim 64, where the
+// exponentials (two per matrix product) leave more to hide: 4K, batch 2, 32/8
+// heads 380 -> 330 us.  (Four spill: 1,260 us; so do the two-term forms, and
+// the dQ kernel, at three.)
+template <int D, int NW, int HM>
+constexpr int kWavesPerSimd = D == 64 && NW == 4 && HM == 0 ? 3 : 2;
+
 template <int D, int NW, int NS, int HM>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void fwd_bf16_kernel(
-    const AttnArgs a) {
+__global__ __launch_bounds__(NW * 64)
+    __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D, NW, HM>, kWavesPerSimd<D, NW, HM>))) void fwd_bf16_kernel(
+        const AttnArgs a) {
   constexpr int BM = NW * 32, BN = 64, KS = D / 16, DT = D / 32;
   constexpr uint32_t RB = D * 2, TB = BN * RB;  // row and tile bytes in LDS
   constexpr int STAGE = 2 * BN * D;             // K tile + V tile (elements), swizzled rows
@@ -378,9 +387,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 template <int D, int NW, int NS>
 void launch_hm(const AttnArgs& a, int n, hipStream_t s) {
   const int hm = !(a.hilo & kHiloPv) ? 0 : (a.hilo & kHiloAdaptive) ? 2 : 1;
-  if (hm == 0) hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, NS, 0>), dim3(n), dim3(NW * 64), 0, s, a);
-  else if (hm == 1) hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, NS, 1>), dim3(n), dim3(NW * 64), 0, s, a);
-  else hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, NS, 2>), dim3(n), dim3(NW * 64), 0, s, a);
+  if constexpr (!(D == 64 && NW == kQRowsLongBf16 / 32)) {  // (fwd_short_always)
+    if (hm == 0) hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, NS, 0>), dim3(n), dim3(NW * 64), 0, s, a);
+  }
+  if (hm == 1) hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, NS, 1>), dim3(n), dim3(NW * 64), 0, s, a);
+  if (hm == 2) hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, NS, 2>), dim3(n), dim3(NW * 64), 0, s, a);
 }
 
 template <int D>
@@ -394,6 +405,7 @@ void launch_rows(const AttnArgs& a, int rows, int n, hipStream_t s) {
 hipError_t launch_fwd_bf16(const AttnArgs& a, int head_dim, int rows, hipStream_t s) {
   const int n = workgroups_for(a.total_tiles * a.heads * a.batch);
   if (n == 0) return hipSuccess;
+  if (rows != kQRowsShortBf16 && fwd_short_always(head_dim, a.hilo)) return hipErrorInvalidValue;
   if (head_dim == 128) launch_rows<128>(a, rows, n, s);
   else launch_rows<64>(a, rows, n, s);
   return hipGetLastError();
