@@ -39,9 +39,10 @@ bdlm_status hip_fail(hipError_t e, const char* what) {
 }
 
 // ---- per-thread kernel timing (bdlm_timing_enable / bdlm_timing_collect)
-enum KernelId { kKFwdBf16 = 0, kKFwdF32, kKMerge, kKBwdDqF32, kKBwdBf16, kKBwdDq, kKBwdF32, kKBwdSum, kKCount };
-const char* const kKernelNames[kKCount] = {"fwd_bf16",    "fwd_f32",     "lse_merge",    "bwd_dq_f32",
-                                           "bwd_dkdv_bf16", "bwd_dq_bf16", "bwd_dkdv_f32", "bwd_dkdv_sum"};
+enum KernelId { kKFwdBf16 = 0, kKFwdF32, kKMerge, kKBwdDqF32, kKBwdBf16, kKBwdDq, kKBwdF32, kKCount };
+// (the dK/dV records include the sum over chunks, where there are any)
+const char* const kKernelNames[kKCount] = {"fwd_bf16",      "fwd_f32",     "lse_merge",   "bwd_dq_f32",
+                                           "bwd_dkdv_bf16", "bwd_dq_bf16", "bwd_dkdv_f32"};
 struct TimingRec {
   int id;
   hipEvent_t a, b;
@@ -209,18 +210,21 @@ int bf16_query_rows(const bdlm_problem* p, int n_k, const bdlm_range* k_ranges, 
 // longest walk, not the card, sets the kernel's time.  Walks longer than the
 // average load per CU are then cut into chunks of that length (fp32: a quarter
 // of it, as its workgroups are lighter), at least min_unit steps, below which
-// a workgroup's fixed cost and its partial sums outweigh the balance.
+// a workgroup's fixed cost and its partial sums outweigh the balance (half as
+// many where every chunk has a CU to itself: 4/2 heads, 256, 512 and 768
+// tokens, 8 -> 4 steps: 26.8 -> 21.6, 27.7 -> 24.3 and 29.3 -> 28.0 us; 1,024
+// tokens no longer fit and lose, 31.5 -> 40.4).
 // Measured: 2,040 tokens, 32/8 heads: dK/dV 375 -> 207 us, and 12 us for the
-// sums (half the average per chunk: 210 and 17; min_unit 16 and 64: no
-// better); 8K, 32/4 heads, adaptive two-term products: 5.5 -> 3.4 ms (half the
-// average: 3.7).  Calls whose longest walk is below the average stay whole.
+// sums (half the average per chunk: 210 and 17); 8K, 32/4 heads, adaptive two-term products: 5.5 -> 3.4 ms (half the
+// average: 3.7); 512 tokens, 4/2 heads: 55 -> 24 us with the sums.  Calls whose
+// longest walk is below the average stay whole.
 struct SplitPlan {
   SplitArgs s;
   size_t counts_bytes = 0, bytes = 0;  // of the workspace: counts, counts + partials
 };
 constexpr int kCus = 256;
 constexpr size_t kMaxSplitBytes = (size_t)256 << 20;
-constexpr int kMinUnitF32 = 8, kMinUnitBf16 = 32;
+constexpr int kMinUnitF32 = 8, kMinUnitBf16 = 8, kMinUnitBf16Idle = 4;
 
 // Does the scheduled dK/dV kernel run this call?
 bool scheduled_dkdv(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges) {
@@ -269,16 +273,25 @@ SplitPlan split_plan(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges,
   for (int j = 0; j < n_k; ++j) {
     const bdlm_range& kr = k_ranges[j];
     const int64_t nt = (kr.len + tile - 1) / tile;
-    int64_t walk = 0;
-    if (unit > 0)
-      for (int64_t t = 0; t < nt; ++t)
-        walk = std::max(walk, walk_steps(p, n_q, q_ranges, kr.stream, kr.pos0 + t * tile,
-                                         kr.pos0 + std::min<int64_t>((t + 1) * tile, kr.len) - 1));
+    // walk[t] <= walk - fall t: the first tile's walk (or the longest one) and the slowest fall from it
+    int64_t walk = 0, fall = 0;
+    if (unit > 0) {
+      std::vector<int64_t> w((size_t)nt);
+      for (int64_t t = 0; t < nt; ++t) {
+        w[t] = walk_steps(p, n_q, q_ranges, kr.stream, kr.pos0 + t * tile,
+                          kr.pos0 + std::min<int64_t>((t + 1) * tile, kr.len) - 1);
+        walk = std::max(walk, w[t]);
+      }
+      fall = nt > 1 ? walk : 0;
+      for (int64_t t = 1; t < nt; ++t) fall = std::min(fall, (walk - w[t]) / t);
+    }
     const int64_t ch = unit > 0 ? std::max<int64_t>((walk + unit - 1) / unit, 1) : 1;
     pl.s.chunks[j] = (int32_t)ch;
+    pl.s.walk[j] = (int32_t)walk;
+    pl.s.fall[j] = (int32_t)fall;
     wgs += nt * ch;
     if (ch > 1) {
-      slots += nt * ch;
+      slots += slots_before(nt, walk, fall, unit);
       chunked += nt;
     }
   }
@@ -313,8 +326,13 @@ int64_t split_unit(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges, s
   // (workgroups that fit a CU side by side: two at head_dim 64, bf16)
   const int64_t average = total / (!f32 && p->head_dim == 64 ? 2 * kCus : kCus);
   const bdlm_range joint[2] = {{BDLM_CLEAN, 0, 0, p->L, 0}, {BDLM_CORRUPTED, 0, 0, p->L, 0}};
-  for (int64_t unit = f32 ? std::max<int64_t>(kMinUnitF32, average / 4) : std::max<int64_t>(kMinUnitBf16, average);
-       longest > average && longest > unit; unit *= 2) {
+  int64_t unit = f32 ? std::max<int64_t>(kMinUnitF32, average / 4) : std::max<int64_t>(kMinUnitBf16, average);
+  if (!f32 && average < kMinUnitBf16) {
+    // a nearly idle card: shorter chunks as long as every workgroup has a CU to itself
+    const int64_t u = std::max<int64_t>(kMinUnitBf16Idle, average);
+    if (split_plan(p, n_q, q_ranges, 2, joint, u).s.wgs_per_pair * pairs <= kCus) unit = u;
+  }
+  for (; longest > average && longest > unit; unit *= 2) {
     *bytes = split_plan(p, n_q, q_ranges, 2, joint, unit).bytes;
     if (*bytes <= kMaxSplitBytes) return unit;
   }
@@ -643,23 +661,19 @@ bdlm_status attn_bwd_impl(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
       ak.n_q = 0;
       for (int i = 0; i < n_q; ++i)
         if (a.qr[i].len > 0) ak.qr[ak.n_q++] = a.qr[i];
-      return launch_bwd_dkdv(ak, p->head_dim, stream);
+      const hipError_t le = launch_bwd_dkdv(ak, p->head_dim, stream);
+      return le != hipSuccess || plan.bytes == 0 ? le : launch_bwd_dkdv_sum(a, p->head_dim, stream);
     });
     if (e != hipSuccess) return hip_fail(e, "backward dK/dV launch");
-    if (plan.bytes > 0) {
-      e = timed(kKBwdSum, stream, [&] { return launch_bwd_dkdv_sum(a, p->head_dim, stream); });
-      if (e != hipSuccess) return hip_fail(e, "backward dK/dV sum launch");
-    }
   } else {
     // The dQ kernel leaves D in the workspace for the dK/dV kernel.
     e = timed(kKBwdDqF32, stream, [&] { return launch_bwd_dq_f32(aq, p->head_dim, stream); });
     if (e != hipSuccess) return hip_fail(e, "backward dQ launch");
-    e = timed(kKBwdF32, stream, [&] { return launch_bwd_dkv_f32(a, p->head_dim, stream); });
+    e = timed(kKBwdF32, stream, [&] {
+      const hipError_t le = launch_bwd_dkv_f32(a, p->head_dim, stream);
+      return le != hipSuccess || plan.bytes == 0 ? le : launch_bwd_sum_f32(a, p->head_dim, stream);
+    });
     if (e != hipSuccess) return hip_fail(e, "backward dK/dV launch");
-    if (plan.bytes > 0) {
-      e = timed(kKBwdSum, stream, [&] { return launch_bwd_sum_f32(a, p->head_dim, stream); });
-      if (e != hipSuccess) return hip_fail(e, "backward dK/dV sum launch");
-    }
   }
   return BDLM_OK;
 }

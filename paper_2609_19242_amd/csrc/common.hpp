@@ -158,7 +158,14 @@ struct SplitArgs {
   int32_t* counts;         // chunks at work, at the slot of a tile's chunk 0
   void* partials;
   int32_t chunks[kMaxK];
+  int32_t walk[kMaxK], fall[kMaxK];  // tile t of range r walks at most walk[r] - fall[r] t steps
 };
+
+// Slots of the tiles before tile t of a range: the integral of an upper bound
+// of the chunks per tile, (walk - fall t) / unit + 1.
+__host__ __device__ inline int64_t slots_before(int64_t t, int64_t walk, int64_t fall, int64_t unit) {
+  return (2 * t * (walk + unit) - fall * t * (t - 1) + 2 * unit - 1) / (2 * unit);
+}
 
 // Workgroups that share a walk of n steps: about `unit` steps each, at most max_chunks.
 __host__ __device__ inline int chunks_of(int n, int unit, int max_chunks) {

@@ -27,13 +27,16 @@ __device__ inline bool key_tile_item(const AttnArgs& a, int wg, KeyTileItem& it)
     it.r = r;
     if (rank < nw) break;
     rank -= nw;
-    if (ch > 1) base += nw;
+    if (ch > 1) base += slots_before(a.kr[r].ntiles, a.split.walk[r], a.split.fall[r], a.split.unit);
   }
   const int ch = a.split.chunks[it.r];
   const int nt = imax(a.kr[it.r].ntiles, 1);
   it.chunk = rank / nt;
   it.t = rank - it.chunk * nt;
-  it.slot = (int64_t)bk * a.split.slots_per_pair + base + (int64_t)it.t * ch;
+  it.slot = 0;
+  if (ch > 1)
+    it.slot = (int64_t)bk * a.split.slots_per_pair + base +
+              slots_before(it.t, a.split.walk[it.r], a.split.fall[it.r], a.split.unit);
   return true;
 }
 
@@ -56,10 +59,10 @@ __device__ inline void sum_item(const AttnArgs& a, int n, SumItem& it) {
     if (ch <= 1) continue;
     if (tile < a.kr[r].ntiles) break;
     tile -= a.kr[r].ntiles;
-    it.slot += (int64_t)a.kr[r].ntiles * ch;
+    it.slot += slots_before(a.kr[r].ntiles, a.split.walk[r], a.split.fall[r], a.split.unit);
   }
   it.t = tile;
-  it.slot += (int64_t)tile * a.split.chunks[it.r];
+  it.slot += slots_before(tile, a.split.walk[it.r], a.split.fall[it.r], a.split.unit);
 }
 
 }  // namespace bdlm
