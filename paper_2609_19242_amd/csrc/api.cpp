@@ -204,6 +204,17 @@ int bf16_query_rows(const bdlm_problem* p, int n_k, const bdlm_range* k_ranges, 
   return walk <= short_walk ? kQRowsShortBf16 : kQRowsLongBf16;
 }
 
+// Query tile of the bf16 forward: 128 rows shared by two teams when the call
+// has few such tiles (a choice by the queries alone, so that a row's sums are
+// the same whichever key ranges are in the call).
+QTile fwd_query_tile(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges, int n_k, const bdlm_range* k_ranges) {
+  int64_t tiles = 0;
+  for (int i = 0; i < n_q; ++i) tiles += (q_ranges[i].len + kQRowsShortBf16 - 1) / kQRowsShortBf16;
+  if (tiles * p->heads * p->batch <= kTeamWgs) return QTile{kQRowsShortBf16, 2};
+  if (fwd_short_always(p->head_dim, p->hilo)) return QTile{kQRowsShortBf16, 1};
+  return QTile{bf16_query_rows(p, n_k, k_ranges, kFwdShortWalk), 1};
+}
+
 // How the dK/dV walks of a backward are cut (SplitArgs).  A key tile's walk
 // covers the queries that see it: every query for the first clean keys, one
 // block for corrupted keys.  With few (batch, KV head, tile) workgroups the
@@ -396,17 +407,16 @@ bdlm_status bdlm_attn_fwd(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
     a.kr[j].k = k[j];
     a.kr[j].v = v[j];
   }
-  const int rows = p->dtype == BDLM_F32              ? kRowsF32
-                   : fwd_short_always(p->head_dim, p->hilo) ? kQRowsShortBf16
-                                                            : bf16_query_rows(p, n_k, k_ranges, kFwdShortWalk);
-  const int64_t tiles = tile_ranges(a.qr, n_q, rows);
+  const QTile qt =
+      p->dtype == BDLM_F32 ? QTile{kRowsF32, 1} : fwd_query_tile(p, n_q, q_ranges, n_k, k_ranges);
+  const int64_t tiles = tile_ranges(a.qr, n_q, qt.rows);
   if ((st = check_grid(tiles, (int64_t)p->heads * p->batch)) != BDLM_OK) return st;
   a.total_tiles = (int32_t)tiles;
   a.interleave = 1;
   for (int i = 1; i < n_q; ++i)
     if (a.qr[i].ntiles != a.qr[0].ntiles) a.interleave = 0;
   const hipError_t e = p->dtype == BDLM_BF16
-                           ? timed(kKFwdBf16, stream, [&] { return launch_fwd_bf16(a, p->head_dim, rows, stream); })
+                           ? timed(kKFwdBf16, stream, [&] { return launch_fwd_bf16(a, p->head_dim, qt, stream); })
                            : timed(kKFwdF32, stream, [&] { return launch_fwd_f32(a, p->head_dim, stream); });
   if (e != hipSuccess) return hip_fail(e, "forward launch");
   return BDLM_OK;
@@ -607,9 +617,9 @@ bdlm_status attn_bwd_impl(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
   // The dQ kernel walks query tiles (of its own height).
   AttnArgs aq = a;
   const int dq_rows = p->dtype == BDLM_BF16 ? bf16_query_rows(p, n_k, k_ranges, kDqShortWalk) : kRowsF32;
-  const int64_t qt = tile_ranges(aq.qr, n_q, dq_rows);
-  if ((st = check_grid(qt, (int64_t)p->heads * p->batch)) != BDLM_OK) return st;
-  aq.total_tiles = (int32_t)qt;
+  const int64_t dq_tiles = tile_ranges(aq.qr, n_q, dq_rows);
+  if ((st = check_grid(dq_tiles, (int64_t)p->heads * p->batch)) != BDLM_OK) return st;
+  aq.total_tiles = (int32_t)dq_tiles;
   aq.interleave = 1;
   for (int i = 1; i < n_q; ++i)
     if (aq.qr[i].ntiles != aq.qr[0].ntiles) aq.interleave = 0;

@@ -246,7 +246,11 @@ __host__ __device__ inline bool xcd_pair_item(int wg, int nbk, int T, bool inter
 inline int workgroups_for(int items) { return (items + 7) & ~7; }
 
 // Launchers (defined in the .hip files).  All return hipSuccess or the launch error.
-hipError_t launch_fwd_bf16(const AttnArgs& a, int head_dim, int rows, hipStream_t s);
+// Query tile of the bf16 forward: rows per workgroup, teams (fwd_bf16.hip).
+struct QTile {
+  int rows, teams;
+};
+hipError_t launch_fwd_bf16(const AttnArgs& a, int head_dim, QTile q, hipStream_t s);
 hipError_t launch_fwd_f32(const AttnArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_merge(const MergeArgs& a, int head_dim, int part_dtype, int out_dtype, hipStream_t s);
 hipError_t launch_bwd_bf16(const AttnArgs& a, int head_dim, hipStream_t s);
@@ -347,6 +351,7 @@ constexpr int kQRowsLongBf16 = 256;
 constexpr int kQRowsShortBf16 = 128;
 constexpr int64_t kFwdShortWalk = 16384;  // keys a row may see for the 128-row forward
 constexpr int64_t kDqShortWalk = 8192;    // ... and for the 128-row dQ kernel
+constexpr int64_t kTeamWgs = 256;         // 128-row tiles of a call at most for two teams (forward)
 // (the single-term forward at head_dim 64 always takes 128 rows: its 4-wave
 // workgroups run at three waves per SIMD; 64K, 16/8 heads 19.7 -> 16.9 ms)
 inline bool fwd_short_always(int head_dim, int hilo) { return head_dim == 64 && !(hilo & kHiloPv); }

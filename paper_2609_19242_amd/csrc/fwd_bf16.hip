@@ -22,6 +22,14 @@
 // row reads and the transpose reads are free of bank conflicts.  A wave none
 // of whose rows sees a partly visible tile skips it.
 //
+// Two teams.  Where a call has few 128-row tiles, the walk of one workgroup,
+// not the card, sets the time.  A workgroup then has two teams of four waves
+// that own the same 128 rows and take the visible key tiles in turn, each with
+// its own two K/V stages; at the end team 1 hands its row max, sums and O^T to
+// team 0 through LDS.  (4/2 heads, 256 / 512 / 1,024 tokens: 16.5 / 21.2 /
+// 30.4 -> 15.7 / 18.9 / 25.5 us.  The dQ kernel gained nothing: 19.8 / 25.0 /
+// 34.9 and 21.1 / 25.4 / 33.4 us with teams.)
+//
 // Masking: each lane's visible keys in a key range are one position interval
 // (the rules in common.hpp).  Tiles inside every lane's interval run without a
 // mask test, tiles outside all of them are never visited, and the O(1) tiles
@@ -41,11 +49,11 @@ constexpr float kSumLimit = 18446744073709551616.f;  // 2^64: a lane's tile sum 
 // heads 380 -> 330 us.  (Four spill: 1,260 us; so do the two-term forms, and
 // the dQ kernel, at three.)
 template <int D, int NW, int HM>
-constexpr int kWavesPerSimd = D == 64 && NW == 4 && HM == 0 ? 3 : 2;
+constexpr int kWavesPerSimd = D == 64 && NW == 4 && HM == 0 ? 3 : 2;  // (NW: waves of all teams)
 
-template <int D, int NW, int NS, int HM>
-__global__ __launch_bounds__(NW * 64)
-    __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D, NW, HM>, kWavesPerSimd<D, NW, HM>))) void fwd_bf16_kernel(
+template <int D, int NW, int NS, int HM, int NT>
+__global__ __launch_bounds__(NT * NW * 64)
+    __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D, NT * NW, HM>, kWavesPerSimd<D, NT * NW, HM>))) void fwd_bf16_kernel(
         const AttnArgs a) {
   constexpr int BM = NW * 32, BN = 64, KS = D / 16, DT = D / 32;
   constexpr uint32_t RB = D * 2, TB = BN * RB;  // row and tile bytes in LDS
@@ -54,9 +62,11 @@ __global__ __launch_bounds__(NW * 64)
   // waves 0 .. NW/2 - 1 copy K and the others V, IPW instructions each.
   constexpr int TI = BN * D / 8 / 64, IPW = TI / (NW / 2);
   static_assert(TI % (NW / 2) == 0, "whole copy instructions per wave");
-  __shared__ __attribute__((aligned(256))) bf16 lds[NS * STAGE];
+  __shared__ __attribute__((aligned(256))) bf16 lds_all[NT * NS * STAGE];
 
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int team = wv / NW, w = wv % NW;  // NT teams of NW waves
+  bf16* const lds = lds_all + team * (NS * STAGE);
   const int l32 = lane & 31, half = lane >> 5;
   const int G = lane >> 4, sl = lane & 15;
 
@@ -95,10 +105,15 @@ __global__ __launch_bounds__(NW * 64)
     int j, t, t1, f0, f1;
     bool have;
   };
-  auto next_tile = [&](KCur c) -> KCur {
+  auto next_one = [&](KCur c) __attribute__((always_inline)) -> KCur {
     if (!c.have) return c;
     if (++c.t < c.t1) return c;
     c.have = find_key_tile(a, c.j + 1, qr.stream, pq0, pq1, BN, c.j, c.t, c.t1, c.f0, c.f1);
+    return c;
+  };
+  auto next_tile = [&](KCur c) __attribute__((always_inline)) -> KCur {  // the team's next: every NT-th tile
+    c = next_one(c);
+    if constexpr (NT > 1) c = next_one(c);
     return c;
   };
   // The copy cursor runs NS - 1 tiles ahead of the compute cursor and carries
@@ -122,12 +137,13 @@ __global__ __launch_bounds__(NW * 64)
   };
   auto copy_next = [&](CopyCur cc) -> CopyCur {
     if (!cc.c.have) return cc;
-    if (++cc.c.t < cc.c.t1) {
-      cc.src += (int64_t)BN * HKV * D;
-      cc.rows_left -= BN;
+    if (cc.c.t + NT < cc.c.t1) {
+      cc.c.t += NT;
+      cc.src += (int64_t)(NT * BN) * HKV * D;
+      cc.rows_left -= NT * BN;
       return cc;
     }
-    cc.c.have = find_key_tile(a, cc.c.j + 1, qr.stream, pq0, pq1, BN, cc.c.j, cc.c.t, cc.c.t1, cc.c.f0, cc.c.f1);
+    cc.c = next_tile(cc.c);
     return copy_seek(cc);
   };
   // LDS-DMA copy of the cursor's tile into stage st (empty copies past the
@@ -158,6 +174,11 @@ __global__ __launch_bounds__(NW * 64)
   // stage gains nothing over two except a shorter wait at the barrier.)
   KCur c0;
   c0.have = find_key_tile(a, 0, qr.stream, pq0, pq1, BN, c0.j, c0.t, c0.t1, c0.f0, c0.f1);
+  if constexpr (NT > 1) {
+    if (team == 1) c0 = next_one(c0);
+  }
+  // (teams: every wave runs as many rounds as team 0, the first to be dealt a tile, for the barriers)
+  int rounds = NT > 1 ? (count_key_tiles(a, qr.stream, pq0, pq1, BN) + NT - 1) / NT : 0;
   CopyCur cp = copy_seek(CopyCur{c0, any_src, 0});
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s) {
@@ -167,18 +188,19 @@ __global__ __launch_bounds__(NW * 64)
   vm_wait_barrier<IPW * (NS - 2)>();
   int cur = 0;
   int lane_lo = 0, lane_w = 0, lane_j = -1;
-  while (c0.have) {
+  while (NT > 1 ? rounds > 0 : c0.have) {
+    if constexpr (NT > 1) --rounds;
     copy_tile(lds + (cur == 0 ? NS - 1 : cur - 1) * STAGE, cp);
     const int j = c0.j, t = c0.t, f0 = c0.f0, f1 = c0.f1;
-    if (lane_j != j) {  // this lane's visible key interval inside range j
+    if (lane_j != j && (NT == 1 || c0.have)) {  // this lane's visible key interval inside range j
       lane_key_interval(a, j, qr.stream, pq, lane_lo, lane_w);
       lane_j = j;
     }
 
     // On a partly visible tile, a wave none of whose rows sees any of the
     // tile's keys skips it (it still copies and meets the barrier).
-    bool skip = false;
-    if (!(t >= f0 && t < f1)) {
+    bool skip = NT > 1 && !c0.have;
+    if (!skip && !(t >= f0 && t < f1)) {
       const int kstart = a.kr[j].pos0 + t * BN - lane_lo;
       skip = __builtin_amdgcn_ballot_w64(lane_w > 0 && kstart < lane_w && kstart + BN > 0) == 0;
     }
@@ -347,6 +369,40 @@ __global__ __launch_bounds__(NW * 64)
   // the workgroup's LDS is released.
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
 
+  if constexpr (NT > 1) {
+    // Merge the teams: team 1's O^T, row max and sums through LDS (the stages
+    // are free once every wave has left the walk).
+    __syncthreads();
+    f32x4* const part = (f32x4*)lds_all + w * ((4 * DT + 1) * 64) + lane;
+    if (team == 1) {
+#pragma unroll
+      for (int d = 0; d < DT; ++d)
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4)
+          part[(4 * d + g4) * 64] = f32x4{acc[d][4 * g4], acc[d][4 * g4 + 1], acc[d][4 * g4 + 2], acc[d][4 * g4 + 3]};
+      part[4 * DT * 64] = f32x4{m_run, l_run, 0.f, 0.f};
+    }
+    __syncthreads();
+    if (team == 0) {
+      const f32x4 ml = part[4 * DT * 64];
+      const float m = fmaxf(m_run, ml[0]);
+      const float a0 = m_run == -INFINITY ? 0.f : exp2f_fast(m_run - m);
+      const float a1 = ml[0] == -INFINITY ? 0.f : exp2f_fast(ml[0] - m);
+      l_run = l_run * a0 + ml[1] * a1;
+      m_run = m;
+#pragma unroll
+      for (int d = 0; d < DT; ++d)
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {
+          const f32x4 x = part[(4 * d + g4) * 64];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[d][4 * g4 + e] = acc[d][4 * g4 + e] * a0 + x[e] * a1;
+        }
+    }
+    __syncthreads();
+    if (team != 0) return;
+  }
+
   // Epilogue: O = O^T / l (bf16), LSE = ln(2) * (m + log2 l); empty rows O = 0, LSE = -inf.
   const float l_tot = l_run + partner(l_run);
   const bool empty = !(l_tot > 0.f);
@@ -367,7 +423,7 @@ __global__ __launch_bounds__(NW * 64)
   } else {
     // bf16 O through LDS (the stages are free: every wave's copies have landed
     // and every wave has left the walk once all meet this barrier).
-    asm volatile("s_barrier" ::: "memory");
+    if constexpr (NT == 1) asm volatile("s_barrier" ::: "memory");  // (teams have met)
     const int wrow0 = row0 + w * 32;
     store_rows_bf16_via_lds<D>(
         lds_addr(lds) + (uint32_t)w * (D * 64), [&](int d, int g4, int e) { return acc[d][g4 * 4 + e] * inv; },
@@ -384,30 +440,33 @@ __global__ __launch_bounds__(NW * 64)
 // two-term on the 16-key chunks holding a large probability.
 // NW waves of 32 rows; NS = 3 stages (96 KB: one 8-wave workgroup per CU)
 // or 2 (64 KB: two 4-wave workgroups per CU).
-template <int D, int NW, int NS>
+// NT teams: two with 4 waves and 2 stages each.
+template <int D, int NW, int NS, int NT>
 void launch_hm(const AttnArgs& a, int n, hipStream_t s) {
   const int hm = !(a.hilo & kHiloPv) ? 0 : (a.hilo & kHiloAdaptive) ? 2 : 1;
+  const dim3 threads(NT * NW * 64);
   if constexpr (!(D == 64 && NW == kQRowsLongBf16 / 32)) {  // (fwd_short_always)
-    if (hm == 0) hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, NS, 0>), dim3(n), dim3(NW * 64), 0, s, a);
+    if (hm == 0) hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, NS, 0, NT>), dim3(n), threads, 0, s, a);
   }
-  if (hm == 1) hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, NS, 1>), dim3(n), dim3(NW * 64), 0, s, a);
-  if (hm == 2) hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, NS, 2>), dim3(n), dim3(NW * 64), 0, s, a);
+  if (hm == 1) hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, NS, 1, NT>), dim3(n), threads, 0, s, a);
+  if (hm == 2) hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, NS, 2, NT>), dim3(n), threads, 0, s, a);
 }
 
 template <int D>
-void launch_rows(const AttnArgs& a, int rows, int n, hipStream_t s) {
-  if (rows == kQRowsShortBf16) launch_hm<D, kQRowsShortBf16 / 32, 2>(a, n, s);
-  else launch_hm<D, kQRowsLongBf16 / 32, 3>(a, n, s);
+void launch_rows(const AttnArgs& a, QTile q, int n, hipStream_t s) {
+  if (q.teams == 2) launch_hm<D, kQRowsShortBf16 / 32, 2, 2>(a, n, s);
+  else if (q.rows == kQRowsShortBf16) launch_hm<D, kQRowsShortBf16 / 32, 2, 1>(a, n, s);
+  else launch_hm<D, kQRowsLongBf16 / 32, 3, 1>(a, n, s);
 }
 
 }  // namespace
 
-hipError_t launch_fwd_bf16(const AttnArgs& a, int head_dim, int rows, hipStream_t s) {
+hipError_t launch_fwd_bf16(const AttnArgs& a, int head_dim, QTile q, hipStream_t s) {
   const int n = workgroups_for(a.total_tiles * a.heads * a.batch);
   if (n == 0) return hipSuccess;
-  if (rows != kQRowsShortBf16 && fwd_short_always(head_dim, a.hilo)) return hipErrorInvalidValue;
-  if (head_dim == 128) launch_rows<128>(a, rows, n, s);
-  else launch_rows<64>(a, rows, n, s);
+  if (q.rows != kQRowsShortBf16 && fwd_short_always(head_dim, a.hilo)) return hipErrorInvalidValue;
+  if (head_dim == 128) launch_rows<128>(a, q, n, s);
+  else launch_rows<64>(a, q, n, s);
   return hipGetLastError();
 }
 

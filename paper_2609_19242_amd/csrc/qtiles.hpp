@@ -79,6 +79,17 @@ __device__ inline bool find_key_tile(const AttnArgs& a, int jj, int qs, int pq0,
   return false;
 }
 
+// Key tiles of all ranges that the query tile can see.
+__device__ inline int count_key_tiles(const AttnArgs& a, int qs, int pq0, int pq1, int BN) {
+  int n = 0;
+  for (int j = 0; j < a.n_k; ++j) {
+    int a0, a1, b0, b1;
+    key_tile_span(a, j, qs, pq0, pq1, BN, a0, a1, b0, b1);
+    n += a1 - a0;
+  }
+  return n;
+}
+
 // This lane's visible key interval [lo, lo + w) inside key range j (w may be 0).
 __device__ inline void lane_key_interval(const AttnArgs& a, int j, int qs, int pq, int& lo, int& w) {
   const KRangeArg& kr = a.kr[j];
