@@ -20,7 +20,7 @@
 //    chunk order.
 // Measured against one thread per query row (dQ) or key row (dK, dV), both
 // kernels together: L = 256, 2/2 heads, d 64: 10.7 ms -> 44 us; L = 1125, 8/2
-// heads, d 128: 621 -> 0.71 ms.
+// heads, d 128: 621 -> 0.55 ms.
 #include "f64tile.hpp"
 #include "ktiles.hpp"
 #include "qtiles.hpp"
@@ -157,38 +157,44 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
   const int row0 = it.t * 16, nvalid = imin(16, kr.len - row0);
   const int ki = imin(i, nvalid - 1), pk = kr.pos0 + row0 + ki;
 
-  // Units of the walk: (query range, 16-query tile, head of the group).
+  // Units of the walk: (query range, 16-query tile, head of the group), from
+  // the end of the first two ranges down, side by side (walk_plan), then the
+  // other ranges.  The visible queries of every key tile extend to the end of
+  // a range, so the same chunk of all tiles, which run together, reads the
+  // same rows, from L2.
   const int kp0 = kr.pos0 + row0, kp1 = kr.pos0 + row0 + nvalid - 1;
+  // Tiles [t0, t1) of query range q that some key of this tile sees, and the
+  // rows [i0, i1) of the range that every one of them sees.
   struct Span {
-    int t0, t1, f0, f1;
+    int t0, t1, i0, i1;
   };
   auto span = [&](int q) __attribute__((always_inline)) -> Span {
+    Span s{0, 0, 0, 0};
+    if (q >= a.n_q) return s;
     const QRangeArg& qr = a.qr[q];
     int lo0, hi0, lo1, hi1;
     query_interval(qr.stream, kr.stream, kp0, rule_of(a), lo0, hi0);
     query_interval(qr.stream, kr.stream, kp1, rule_of(a), lo1, hi1);
     const int u0 = imax(lo0 - qr.pos0, 0), u1 = imin(hi1 - qr.pos0, qr.len);
-    Span s{0, 0, 0, 0};
     if (u1 > u0) {
       s.t0 = u0 / 16;
       s.t1 = (u1 + 15) / 16;
-      const int i0 = imax(lo1 - qr.pos0, 0), i1 = imin(hi0 - qr.pos0, qr.len);
-      if (i1 > i0) {
-        s.f0 = (i0 + 15) / 16;
-        s.f1 = i1 / 16;
-      }
+      s.i0 = imax(lo1 - qr.pos0, 0);
+      s.i1 = imin(hi0 - qr.pos0, qr.len);
     }
     return s;
   };
-  int units = 0;
-  for (int q = 0; q < a.n_q; ++q) {
+  const Span s0 = span(0), s1 = span(1);
+  const WalkPlan wp = walk_plan(s0.t0, s0.t1, s1.t0, s1.t1, a.group);
+  int units = wp.nsteps;
+  for (int q = 2; q < a.n_q; ++q) {
     const Span s = span(q);
     units += (s.t1 - s.t0) * a.group;
   }
   const int nch = a.split.chunks[it.r] > 1 ? chunks_of(units, a.split.unit, a.split.chunks[it.r]) : 1;
   if (it.chunk == 0 && tid == 0 && a.split.chunks[it.r] > 1) a.split.counts[it.slot] = nch;
   if (it.chunk >= nch) return;
-  const int n0 = (int)((int64_t)units * it.chunk / nch), n1 = (int)((int64_t)units * (it.chunk + 1) / nch);
+  const int n0 = it.chunk * a.split.unit, n1 = it.chunk + 1 < nch ? n0 + a.split.unit : units;
 
   const int64_t koff = (((int64_t)it.b * kr.bstride + row0) * HKV + it.kvh) * D;
   stage_row_operands<D>(lds, (const float*)kr.k + koff, HKV * D, nvalid, tid, kWaves * 64);
@@ -199,23 +205,32 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
   AccTiles<D> dk, dv;
   dk.zero();
   dv.zero();
-  int q = -1, q_first = 0, q_end = 0;  // the current range's units [q_first, q_end)
-  Span sp{0, 0, 0, 0};
-  int qa = 0, qw = 0;  // the queries of the range that see this lane's key
   for (int n = n0 + w; n < n1; n += kWaves) {
-    while (n >= q_end) {
-      sp = span(++q);
-      q_first = q_end;
-      q_end += (sp.t1 - sp.t0) * a.group;
-      const QRangeArg& qr = a.qr[q];
-      int lo, hi;
-      query_interval(qr.stream, kr.stream, pk, rule_of(a), lo, hi);
-      qa = imax(lo, qr.pos0);
-      qw = imax(imin(hi, qr.pos0 + qr.len) - qa, 0);
+    int q, t, hq;
+    Span sp;
+    if (n < wp.nsteps) {
+      const WalkStep ws = walk_step(wp, n);
+      q = ws.q;
+      t = ws.s;
+      hq = ws.hp;
+      sp = q ? s1 : s0;
+    } else {
+      int m = n - wp.nsteps, size = 0;
+      q = 1;
+      do {
+        m -= size;
+        sp = span(++q);
+        size = (sp.t1 - sp.t0) * a.group;
+      } while (m >= size);
+      t = sp.t0 + m / a.group;
+      hq = m % a.group;
     }
     const QRangeArg& qr = a.qr[q];
-    const int tt = (n - q_first) / a.group, t = sp.t0 + tt;
-    const int h = it.kvh * a.group + (n - q_first) - tt * a.group;
+    const int h = it.kvh * a.group + hq;
+    int qlo, qhi;  // the queries of the range that see this lane's key
+    query_interval(qr.stream, kr.stream, pk, rule_of(a), qlo, qhi);
+    qlo = imax(qlo, qr.pos0);
+    const int qw = imax(imin(qhi, qr.pos0 + qr.len) - qlo, 0);
     const int64_t hrow = (int64_t)it.b * H + h;
     const int64_t qoff = (((int64_t)it.b * qr.bstride + t * 16) * H + h) * D;
     const int qrows = imin(16, qr.len - t * 16);
@@ -223,7 +238,6 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
     fl4 qx[NC], ox[NC];
     ColOps<D> cx;
     load_rows<D>(qx, qt, i, g);
-    load_rows<D>(ox, ot, i, g);
     float lse[4], dl[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -232,13 +246,14 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
       dl[r] = qr.delta[hrow * qr.len + row];
     }
     const f64x4 s = row_product<D>(qx, lds, lane);
+    load_rows<D>(ox, ot, i, g);
     cx.load(ot, i, g);
     const f64x4 dp = row_product<D>(ox, lds + OPS, lane);
     bool dead = false;
 #pragma unroll
     for (int r = 0; r < 4; ++r) dead |= lse[r] == -INFINITY;
-    const bool full = t >= sp.f0 && t < sp.f1 && __builtin_amdgcn_ballot_w64(dead) == 0;
-    const int qbase = qr.pos0 + t * 16 - qa;
+    const bool full = t * 16 >= sp.i0 && t * 16 + 16 <= sp.i1 && __builtin_amdgcn_ballot_w64(dead) == 0;
+    const int qbase = qr.pos0 + t * 16 - qlo;
     auto seen_row = [&](int row) { return full || (unsigned)(qbase + row) < (unsigned)qw; };
     f64x4 p, ds;
 #pragma unroll
