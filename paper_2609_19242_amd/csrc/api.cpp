@@ -228,14 +228,16 @@ QTile fwd_query_tile(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges,
 // Measured: 2,040 tokens, 32/8 heads: dK/dV 375 -> 207 us, and 12 us for the
 // sums (half the average per chunk: 210 and 17); 8K, 32/4 heads, adaptive two-term products: 5.5 -> 3.4 ms (half the
 // average: 3.7); 512 tokens, 4/2 heads: 55 -> 24 us with the sums.  Calls whose
-// longest walk is below the average stay whole.
+// longest walk is within kCutSteps (or a third) of the average stay whole, as
+// cutting costs about that much (3,000 tokens, 16/16 heads: 94 steps, 75 on average: 180 us
+// cut, 167 whole; 6,000 tokens, 32/8 heads: 750 and 580: 1,157 and 1,216 us).
 struct SplitPlan {
   SplitArgs s;
   size_t counts_bytes = 0, bytes = 0;  // of the workspace: counts, counts + partials
 };
 constexpr int kCus = 256;
 constexpr size_t kMaxSplitBytes = (size_t)256 << 20;
-constexpr int kMinUnitF32 = 8, kMinUnitBf16 = 8, kMinUnitBf16Idle = 4;
+constexpr int kCutSteps = 25, kMinUnitF32 = 8, kMinUnitBf16 = 8, kMinUnitBf16Idle = 4;
 
 // Does the scheduled dK/dV kernel run this call?
 bool scheduled_dkdv(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges) {
@@ -343,7 +345,8 @@ int64_t split_unit(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges, s
     const int64_t u = std::max<int64_t>(kMinUnitBf16Idle, average);
     if (split_plan(p, n_q, q_ranges, 2, joint, u).s.wgs_per_pair * pairs <= kCus) unit = u;
   }
-  for (; longest > average && longest > unit; unit *= 2) {
+  const int64_t margin = f32 ? 0 : std::min<int64_t>(kCutSteps, average / 3);
+  for (; longest > average + margin && longest > unit; unit *= 2) {
     *bytes = split_plan(p, n_q, q_ranges, 2, joint, unit).bytes;
     if (*bytes <= kMaxSplitBytes) return unit;
   }
