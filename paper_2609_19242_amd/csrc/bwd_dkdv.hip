@@ -274,6 +274,19 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   if (it.chunk >= nch) return;
   const int n0 = it.chunk * a.split.unit, n1 = it.chunk + 1 < nch ? n0 + a.split.unit : wp.nsteps;
   wp.nsteps = n1;  // (steps past the chunk copy nothing)
+  // At head_dim 128 the epilogue's scalars wait in VGPRs, of which the walk
+  // leaves some free (it needs every SGPR: spilled ones, read back each step,
+  // cost 2% at 32K).
+  uint64_t partial_at = nch > 1 ? (uint64_t)(uintptr_t)a.split.partials +
+                                      (uint64_t)((it.slot + it.chunk) * 4 + w) * (2 * DT * 4 * 64 * 16)
+                                : 0;
+  if constexpr (D == 128) {
+    asm volatile("" : "+v"(partial_at));
+    // So does the walk's plan, which only the (vector) step descriptors read.
+    asm volatile("" : "+v"(wp.p0), "+v"(wp.p1), "+v"(wp.p2), "+v"(wp.p3), "+v"(wp.st1), "+v"(wp.st2), "+v"(wp.nsteps));
+    asm volatile("" : "+v"(wp.cnt0), "+v"(wp.cnt1), "+v"(wp.cnt2), "+v"(wp.q00), "+v"(wp.q01), "+v"(wp.q02),
+                      "+v"(wp.npairs));
+  }
 
   // ---- copies.  Instruction i of a wave is instruction (w & 1) * IPW + i of
   // its tensor; the per-lane global offsets are constant over the walk.
@@ -682,9 +695,11 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   // ---- epilogue: dK = scale dK^T^T, dV (bf16 or fp32); unseen keys get zeros
 #pragma unroll
   for (int d = 0; d < DT; ++d) asm volatile("" : "+a"(dka[d]), "+a"(dva[d]));
-  if (nch > 1) {
+  const uint64_t part = ((uint64_t)__builtin_amdgcn_readfirstlane((int)(partial_at >> 32)) << 32) |
+                        (uint32_t)__builtin_amdgcn_readfirstlane((int)partial_at);
+  if (part != 0) {
     // The chunk's partial sums, in register order (whole cache lines per store).
-    f32x4* pp = (f32x4*)a.split.partials + ((it.slot + it.chunk) * 4 + w) * (2 * DT * 4 * 64) + lane;
+    f32x4* pp = (f32x4*)(uintptr_t)part + lane;
 #pragma unroll
     for (int d = 0; d < DT; ++d)
 #pragma unroll
