@@ -13,6 +13,7 @@ there is no fallback path.
 from __future__ import annotations
 
 import ctypes
+import functools
 import math
 import os
 from typing import List, Optional, Sequence
@@ -148,7 +149,8 @@ def _rarr(rs: Sequence[Range]) -> ctypes.Array:
 
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        # torch.cuda.current_stream().cuda_stream without its stream object (4 us of a small call's host time)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -304,13 +306,28 @@ def _joint_ptrs(t: torch.Tensor, L: int):
     return [t.data_ptr(), t.data_ptr() + step]
 
 
+_P2 = ctypes.c_void_p * 2
+
+
+@functools.lru_cache(maxsize=64)
+def _joint_range_array(L: int):
+    """The two ranges of the packed layout as the library takes them (read only)."""
+    return _rarr(joint_ranges(L))
+
+
+def _halves(t: torch.Tensor, half_bytes: int):
+    """Addresses of the corrupted and clean parts of a packed tensor, ``half_bytes`` apart."""
+    a = t.data_ptr()
+    return _P2(a, a + half_bytes)
+
+
 def _expect(name, t, dtype, shape):
     """Reject a tensor of the wrong type, dtype, shape or layout before any pointer reaches the library."""
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor, got {type(t).__name__}")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:  # (a torch.Size is a tuple)
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
@@ -369,9 +386,10 @@ def joint_fwd(q, k, v, block_size: int, clean_intra: int = CLEAN_INTRA_CAUSAL, s
         lse = torch.empty((B, Hq, n), dtype=torch.float32, device=q.device)
     else:
         _on_device(q.device, o=o, lse=lse)
-    r = joint_ranges(L)
-    lp = [lse.data_ptr(), lse.data_ptr() + L * 4]
-    attn_fwd(p, r, _joint_ptrs(q, L), _joint_ptrs(o, L), lp, r, _joint_ptrs(k, L), _joint_ptrs(v, L), stream)
+    r = _joint_range_array(L)
+    nq, nk, eq, eo = L * Hq * D, L * k.shape[2] * D, q.element_size(), o.element_size()
+    _check(lib().bdlm_attn_fwd(ctypes.byref(p), 2, r, _halves(q, nq * eq), _halves(o, nq * eo), _halves(lse, L * 4),
+                               2, r, _halves(k, nk * eq), _halves(v, nk * eq), _stream(stream)))
     return o, lse
 
 
@@ -384,7 +402,7 @@ def joint_bwd(q, k, v, o, lse, do, block_size: int, clean_intra: int = CLEAN_INT
     L = n // 2
     p = make_problem(B, L, block_size, Hq, k.shape[2], D, q.dtype, scale, clean_intra, out_f32, hilo,
                      window, clean_prefix)
-    r = joint_ranges(L)
+    r = _joint_range_array(L)
     odt = torch.float32 if out_f32 else q.dtype
     _expect("o", o, odt, q.shape)
     _expect("lse", lse, torch.float32, (B, Hq, n))
@@ -402,12 +420,17 @@ def joint_bwd(q, k, v, o, lse, do, block_size: int, clean_intra: int = CLEAN_INT
         _on_device(q.device, dq=out[0], dk=out[1], dv=out[2])
     dq, dk, dv = out
     if workspace is None:
-        workspace = torch.empty(attn_bwd_workspace_bytes(p, r), dtype=torch.uint8, device=q.device)
+        nbytes = lib().bdlm_attn_bwd_workspace_bytes(ctypes.byref(p), 2, r)
+        workspace = torch.empty(nbytes, dtype=torch.uint8, device=q.device)
         if stream is not None:  # used on that stream after this call has dropped it
             workspace.record_stream(torch.cuda.ExternalStream(_stream(stream), device=q.device))
-    lp = [lse.data_ptr(), lse.data_ptr() + L * 4]
-    attn_bwd(p, r, _joint_ptrs(q, L), _joint_ptrs(o, L), lp, _joint_ptrs(do, L), _joint_ptrs(dq, L),
-             r, _joint_ptrs(k, L), _joint_ptrs(v, L), _joint_ptrs(dk, L), _joint_ptrs(dv, L), workspace, stream)
+    else:
+        nbytes = workspace.numel() * workspace.element_size()
+    nq, nk, eq, eo = L * Hq * D, L * k.shape[2] * D, q.element_size(), o.element_size()
+    _check(lib().bdlm_attn_bwd(ctypes.byref(p), 2, r, _halves(q, nq * eq), _halves(o, nq * eo), _halves(lse, L * 4),
+                               _halves(do, nq * eq), _halves(dq, nq * eo), 2, r, _halves(k, nk * eq),
+                               _halves(v, nk * eq), _halves(dk, nk * eo), _halves(dv, nk * eo),
+                               workspace.data_ptr(), nbytes, _stream(stream)))
     return dq, dk, dv
 
 
