@@ -38,7 +38,10 @@ constexpr double kLn2D = 0.69314718055994530942;
 __device__ __forceinline__ void mfma64(f64x4& c, double a, double b) {
   asm volatile("s_nop 1\n\tv_mfma_f64_16x16x4_f64 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
-// Before vector code reads c: its last product must have left the matrix core.
+// Before vector code reads c: its last product must have left the matrix core
+// (19 wait states).  The compiler does not see the product in the inline
+// assembly: any use of c that it may add, a copy or a spill included, has to
+// come after this too.
 __device__ __forceinline__ void mfma64_done(f64x4& c) { asm volatile("s_nop 15\n\ts_nop 7" : "+v"(c)); }
 
 // Sum (or any reduction) partners of a C-layout column: lanes i, i+16, i+32, i+48.
@@ -188,10 +191,13 @@ struct AccTiles {
 #pragma unroll
     for (int n = 0; n < D / 16; ++n) t[n] = f64x4{0, 0, 0, 0};
   }
-  // Before vector code reads the accumulators.
+  // Before vector code reads the accumulators (one wait for all of them).
   __device__ __forceinline__ void done() {
-#pragma unroll
-    for (int n = 0; n < D / 16; ++n) mfma64_done(t[n]);
+    if constexpr (D == 128)
+      asm volatile("s_nop 15\n\ts_nop 7"
+                   : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(t[4]), "+v"(t[5]), "+v"(t[6]), "+v"(t[7]));
+    else
+      asm volatile("s_nop 15\n\ts_nop 7" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]));
   }
   __device__ __forceinline__ void scale(double s) {
     done();
@@ -201,7 +207,8 @@ struct AccTiles {
 };
 
 // acc[d][column] += sum over the tile's 16 rows of X[row][d] w[row][column],
-// w in C layout.
+// w in C layout.  Ends with the wait for its products: where its callers' paths
+// meet (col_product_guarded), the compiler copies or spills accumulators.
 template <int D>
 __device__ __forceinline__ void col_product(AccTiles<D>& acc, const ColOps<D>& x, const f64x4& w) {
 #pragma unroll
@@ -211,6 +218,7 @@ __device__ __forceinline__ void col_product(AccTiles<D>& acc, const ColOps<D>& x
 #pragma unroll
       for (int e = 0; e < 4; ++e) mfma64(acc.t[4 * h + e], (double)x.x[kk][h][e], w[kk]);
     }
+  acc.done();
 }
 
 // The same for a tile holding non-finite operands and hidden (row, column)

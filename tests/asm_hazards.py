@@ -1,0 +1,106 @@
+"""Reads assembly listings of the kernels built here for one hazard: the result
+of a v_mfma_f64_16x16x4_f64 that an instruction touches before the matrix core
+has written it.
+
+The hardware does not wait by itself on gfx950: an instruction other than a
+product of the same accumulator (same destination, as its addend) must come at
+least 19 wait states after the product, along every path.  The compiler pads
+builtin products, but cannot see into the inline assembly that the fp32 kernels
+use, nor does it know that a copy or spill of its own reads a product's result.
+"""
+import re
+
+WAIT = 19  # wait states between a 16x16x4 fp64 product and a read (or another write) of its result
+PRODUCT = "v_mfma_f64_16x16x4_f64"
+_REG = re.compile(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+)\b)")
+
+
+def _regs(operand):
+    out = set()
+    for m in _REG.finditer(operand):
+        lo = int(m.group(2) or m.group(4))
+        hi = int(m.group(3) or m.group(4))
+        out |= {(m.group(1), i) for i in range(lo, hi + 1)}
+    return frozenset(out)
+
+
+def functions(listing):
+    """{name: [(line number, label or None, mnemonic, operands)]} of a listing's functions."""
+    out, name, body = {}, None, []
+    for n, raw in enumerate(listing.split("\n"), 1):
+        line = raw.split(";", 1)[0].split("//", 1)[0].strip()
+        m = re.match(r"([.\w$]+):", line)
+        if m:
+            if name is None and m.group(1).startswith("_Z"):
+                name, body = m.group(1), []
+            elif name is not None:
+                body.append((n, m.group(1), None, ()))
+            line = line[m.end():].strip()
+        if name is None or not line:
+            continue
+        if line.startswith("."):
+            if line.startswith((".end_amdhsa_kernel", ".size", ".section")):
+                out[name] = body
+                name = None
+            continue
+        parts = line.split(None, 1)
+        ops = tuple(o.strip() for o in re.split(r",(?![^\[]*\])", parts[1])) if len(parts) > 1 else ()
+        body.append((n, None, parts[0], ops))
+    return out
+
+
+def f64_hazards(body):
+    """[(line of the use, line of the product, wait states between)] of one function, over all its paths."""
+    at_label = {lab: i for i, (_, lab, _, _) in enumerate(body) if lab}
+    found = {}
+    # state: register -> (wait states still missing, line of the product); worklist over instruction indices
+    seen, work = {}, [(0, {})]
+    while work:
+        i, state = work.pop()
+        while i < len(body):
+            line, label, op, ops = body[i]
+            if label is not None:
+                old = seen.get(i, {})
+                merged = dict(old)
+                for r, v in state.items():
+                    if r not in merged or merged[r][0] < v[0]:
+                        merged[r] = v
+                if i in seen and merged == old:
+                    break
+                seen[i] = merged
+                state = dict(merged)
+                i += 1
+                continue
+            touched = set()
+            if op == PRODUCT:
+                dst, addend = _regs(ops[0]), _regs(ops[3])
+                touched = set(_regs(ops[1]) | _regs(ops[2]))
+                if dst != addend:
+                    touched |= dst | addend
+                elif any(r in state for r in dst):
+                    # in flight: right only if it is one product's whole result
+                    if len({state[r][1] for r in dst if r in state}) > 1:
+                        touched |= dst
+            elif not op.startswith("s_") or "v" in "".join(ops):
+                for o in ops:
+                    touched |= _regs(o)
+            for r in touched & state.keys():
+                missing, product = state[r]
+                key = (line, product)
+                found[key] = max(found.get(key, 0), missing)
+            passed = 1
+            if op == "s_nop":
+                passed = int(ops[0], 0) + 1
+            state = {r: (v[0] - passed, v[1]) for r, v in state.items() if v[0] > passed}
+            if op == PRODUCT:
+                for r in _regs(ops[0]):
+                    state[r] = (WAIT, line)
+            if op in ("s_endpgm", "s_setpc_b64"):
+                break
+            if op == "s_branch":
+                work.append((at_label[ops[0]], state))
+                break
+            if op.startswith("s_cbranch"):
+                work.append((at_label[ops[0]], dict(state)))
+            i += 1
+    return sorted((use, product, WAIT - missing) for (use, product), missing in found.items())

@@ -1,0 +1,46 @@
+"""The fp32 kernels' listings, built with the library's own flags, hold no use of
+an fp64 matrix product's result before it is there (see asm_hazards.py)."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2609_19242_amd import build
+from tests.asm_hazards import PRODUCT, f64_hazards, functions
+
+
+def listing(tmp_path, src):
+    try:
+        cc = build.hipcc()
+    except RuntimeError:
+        pytest.skip("hipcc not available")
+    out = str(tmp_path / "kernel.s")
+    subprocess.run([cc, *build.flags(), *build.EXTRA_FLAGS.get(src, []), "-x", "hip", "-S", "--cuda-device-only",
+                    os.path.join(build.CSRC, src), "-o", out], check=True, capture_output=True)
+    return open(out).read()
+
+
+@pytest.mark.parametrize("src", ["fwd_f32.hip", "bwd_f32.hip"])
+def test_products_are_waited_for(tmp_path, src):
+    kernels = {n: b for n, b in functions(listing(tmp_path, src)).items() if any(x[2] == PRODUCT for x in b)}
+    assert len(kernels) == (2 if src == "fwd_f32.hip" else 4), sorted(kernels)
+    bad = {n: f64_hazards(b) for n, b in kernels.items()}
+    assert not any(bad.values()), {n: h for n, h in bad.items() if h}
+
+
+P0 = f"{PRODUCT} v[0:7], v[10:11], v[12:13], v[0:7]"
+SNIPPETS = [  # (body, wait states at the early uses)
+    ([P0, "s_nop 15", "s_nop 2", "v_mov_b32 v20, v7"], []),
+    ([P0, "s_nop 15", "s_nop 1", "v_mov_b32 v20, v7"], [18]),
+    ([P0, P0, f"{PRODUCT} v[30:37], v[10:11], v[12:13], v[30:37]", "s_nop 7", "scratch_store_dwordx2 off, v[36:37], s32"],
+     [8]),
+    ([P0, f"{PRODUCT} v[30:37], v[6:7], v[12:13], v[30:37]"], [0]),
+    ([P0, "s_cbranch_scc1 .LBB0_2", "s_nop 15", "s_nop 7", ".LBB0_2:", "v_add_f64 v[40:41], v[0:1], v[42:43]"], [1]),
+    ([".LBB0_1:", "v_mov_b64_e32 v[20:21], v[2:3]", "s_nop 7", P0, "s_nop 4", "s_branch .LBB0_1"], [6]),
+]
+
+
+@pytest.mark.parametrize("body,early", SNIPPETS, ids=range(len(SNIPPETS)))
+def test_the_reader_counts_wait_states(body, early):
+    text = "_Zkernel:\n" + "\n".join(body) + "\ns_endpgm\n.size _Zkernel\n"
+    assert [h[2] for h in f64_hazards(functions(text)["_Zkernel"])] == early
