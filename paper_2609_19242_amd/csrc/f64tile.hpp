@@ -147,8 +147,9 @@ __device__ __forceinline__ RowTile row_tile(const void* base, int64_t first_row_
   return RowTile{make_rsrc((const float*)base + first_row_elem, (uint32_t)(((int64_t)(nrows - 1) * row_elems + D) * 4)),
                  (uint32_t)(row_elems * 4)};
 }
-__device__ __forceinline__ fl4 buf_f4(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  return __builtin_bit_cast(fl4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+// (the row's offset is part of voff: a scalar offset takes no part in the bounds check)
+__device__ __forceinline__ fl4 buf_f4(__amdgpu_buffer_rsrc_t r, uint32_t voff) {
+  return __builtin_bit_cast(fl4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0));
 }
 // The lane's row operands (row i).
 template <int D>
@@ -156,7 +157,7 @@ __device__ __forceinline__ void load_rows(fl4 (&x)[D / 16], const RowTile& t, in
   uint32_t off = (uint32_t)i * t.stride + 16u * g;
   asm volatile("" : "+v"(off));  // (keeps the loads at this place among the products)
 #pragma unroll
-  for (int c = 0; c < D / 16; ++c) x[c] = buf_f4(t.rsrc, off + 64 * c, 0);
+  for (int c = 0; c < D / 16; ++c) x[c] = buf_f4(t.rsrc, off + 64 * c);
 }
 // The lane's column operands (rows 4 kk + g).
 template <int D>
@@ -168,7 +169,7 @@ struct ColOps {
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
-      for (int h = 0; h < D / 64; ++h) x[kk][h] = buf_f4(t.rsrc, off + 256 * h, 4u * kk * t.stride);
+      for (int h = 0; h < D / 64; ++h) x[kk][h] = buf_f4(t.rsrc, off + 4u * kk * t.stride + 256 * h);
   }
   // Does the tile hold an infinity or NaN?  (wave-uniform)
   __device__ __forceinline__ bool non_finite() const {
@@ -238,7 +239,7 @@ __device__ __forceinline__ void col_product_guarded(AccTiles<D>& acc, const RowT
     for (int h = 0; h < D / 64; ++h)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const fl4 v = buf_f4(t.rsrc, (uint32_t)row * t.stride + 4u * (64 * h + 16 * r + 4 * g), 0);
+        const fl4 v = buf_f4(t.rsrc, (uint32_t)row * t.stride + 4u * (64 * h + 16 * r + 4 * g));
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const double old = acc.t[4 * h + e][r];

@@ -1,17 +1,40 @@
-"""Reads assembly listings of the kernels built here for one hazard: the result
-of a v_mfma_f64_16x16x4_f64 that an instruction touches before the matrix core
-has written it.
+"""Assembly listings of the kernels built here, and two things read in them.
 
-The hardware does not wait by itself on gfx950: an instruction other than a
+f64_hazards: the result of a v_mfma_f64_16x16x4_f64 that an instruction touches
+before the matrix core has written it.  The hardware does not wait by itself on gfx950: an instruction other than a
 product of the same accumulator (same destination, as its addend) must come at
 least 19 wait states after the product, along every path.  The compiler pads
 builtin products, but cannot see into the inline assembly that the fp32 kernels
 use, nor does it know that a copy or spill of its own reads a product's result.
+
+scalar_offset_accesses: buffer accesses with a scalar offset.  The bounds check
+of a buffer resource leaves that offset out, so a row's address has to be in
+the vector offset for rows past the end to read as zeros.
 """
+import os
 import re
+import subprocess
 
 WAIT = 19  # wait states between a 16x16x4 fp64 product and a read (or another write) of its result
 PRODUCT = "v_mfma_f64_16x16x4_f64"
+_CACHE = {}
+
+
+def listing(src):
+    """The listing of a kernel source compiled with the library's own flags (None without a compiler)."""
+    from paper_2609_19242_amd import build
+
+    if src not in _CACHE:
+        try:
+            cc = build.hipcc()
+        except RuntimeError:
+            return None
+        cmd = [cc, *build.flags(), *build.EXTRA_FLAGS.get(src, []), "-x", "hip", "-S", "--cuda-device-only",
+               os.path.join(build.CSRC, src), "-o", "-"]
+        _CACHE[src] = subprocess.run(cmd, check=True, capture_output=True, text=True).stdout
+    return _CACHE[src]
+
+
 _REG = re.compile(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+)\b)")
 
 
@@ -104,3 +127,15 @@ def f64_hazards(body):
                 work.append((at_label[ops[0]], dict(state)))
             i += 1
     return sorted((use, product, WAIT - missing) for (use, product), missing in found.items())
+
+
+def scalar_offset_accesses(body):
+    """(buffer accesses, lines of those whose scalar offset is not 0) of one function."""
+    n, lines = 0, []
+    for line, _, op, ops in body:
+        if op is None or not re.match(r"buffer_(load|store|atomic)", op):
+            continue
+        n += 1
+        if ops[-1].split()[0] not in ("0", "null"):
+            lines.append(line)
+    return n, lines

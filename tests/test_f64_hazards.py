@@ -1,28 +1,16 @@
 """The fp32 kernels' listings, built with the library's own flags, hold no use of
-an fp64 matrix product's result before it is there (see asm_hazards.py)."""
-import os
-import subprocess
-
+an fp64 matrix product's result before it is there (see asm_listing.py)."""
 import pytest
 
-from paper_2609_19242_amd import build
-from tests.asm_hazards import PRODUCT, f64_hazards, functions
-
-
-def listing(tmp_path, src):
-    try:
-        cc = build.hipcc()
-    except RuntimeError:
-        pytest.skip("hipcc not available")
-    out = str(tmp_path / "kernel.s")
-    subprocess.run([cc, *build.flags(), *build.EXTRA_FLAGS.get(src, []), "-x", "hip", "-S", "--cuda-device-only",
-                    os.path.join(build.CSRC, src), "-o", out], check=True, capture_output=True)
-    return open(out).read()
+from tests.asm_listing import PRODUCT, f64_hazards, functions, listing
 
 
 @pytest.mark.parametrize("src", ["fwd_f32.hip", "bwd_f32.hip"])
-def test_products_are_waited_for(tmp_path, src):
-    kernels = {n: b for n, b in functions(listing(tmp_path, src)).items() if any(x[2] == PRODUCT for x in b)}
+def test_products_are_waited_for(src):
+    text = listing(src)
+    if text is None:
+        pytest.skip("hipcc not available")
+    kernels = {n: b for n, b in functions(text).items() if any(x[2] == PRODUCT for x in b)}
     assert len(kernels) == (2 if src == "fwd_f32.hip" else 4), sorted(kernels)
     bad = {n: f64_hazards(b) for n, b in kernels.items()}
     assert not any(bad.values()), {n: h for n, h in bad.items() if h}
