@@ -214,12 +214,14 @@ bdlm_status bdlm_lse_merge_strided(int64_t batch, int64_t rows, int32_t heads, i
 /* Workspace bytes bdlm_attn_bwd takes for these query ranges: per range two
  * fp32 arrays of batch * len * heads values (each rounded up to 256 bytes),
  * LSE * log2(e) and the row dots D = rowsum(dO * O), which every call needs;
- * and, for problems with too few key tiles to fill the card, up to 256 MiB for
- * the partial sums of dK/dV walks that are cut into chunks and run side by
- * side.  bdlm_attn_bwd takes any size from the arrays' up; with less than this
- * function's (or with more key rows than both streams hold) it leaves the
- * walks whole: the same sums in another order, slower.  Ranges whose batch *
- * len * heads exceeds 2^28 are rejected by bdlm_attn_bwd. */
+ * and, for problems with too few key tiles to fill the card, the partial sums
+ * of dK/dV walks that are cut into chunks and run side by side (arrays and
+ * sums together at most BDLM_NOALLOC_SCRATCH_BYTES).  It is enough for any key
+ * ranges, and a key range's dK and dV do not depend on which other ranges are
+ * in the call.  bdlm_attn_bwd takes any size from the arrays' up; with less
+ * than this function's, or with key ranges that overlap, it leaves the walks
+ * whole: the same sums in another order, slower.  Ranges whose batch * len *
+ * heads exceeds 2^28 are rejected by bdlm_attn_bwd. */
 size_t bdlm_attn_bwd_workspace_bytes(const bdlm_problem* p, int32_t n_q, const bdlm_range* q_ranges);
 
 /*
@@ -246,10 +248,10 @@ bdlm_status bdlm_attn_bwd(const bdlm_problem* p,
  * bdlm_attn_bwd without a workspace argument, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc).  Same arguments, arithmetic, kernels and results as
- * bdlm_attn_bwd; the workspace is a library-owned device array of
- * BDLM_NOALLOC_SCRATCH_BYTES bytes instead (one per GPU, held until the process
- * ends; where it has no room for the partial sums of cut walks, they stay
- * whole).  The call allocates nothing.  Query ranges whose D and LSE * log2(e)
+ * bdlm_attn_bwd with the workspace of bdlm_attn_bwd_workspace_bytes(); the
+ * workspace is a library-owned device array of BDLM_NOALLOC_SCRATCH_BYTES bytes
+ * instead (one per GPU, held until the process ends).  The call allocates
+ * nothing.  Query ranges whose D and LSE * log2(e)
  * need more than the array holds (more than about 8M (batch x row x head)
  * entries) are rejected with
  * BDLM_ERR_UNSUPPORTED before anything is enqueued.  The array of the device

@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "split_plan.hpp"
 
 static_assert(BDLM_HILO_PV == bdlm::kHiloPv && BDLM_HILO_DKDV == bdlm::kHiloDkDv && BDLM_HILO_DQ == bdlm::kHiloDq &&
                   BDLM_HILO_ADAPTIVE == bdlm::kHiloAdaptive,
@@ -80,8 +81,6 @@ hipError_t timed(int id, hipStream_t s, F&& f) {
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-
 constexpr int64_t kMaxPos = (int64_t)1 << 30;
 
 bdlm_status check_problem(const bdlm_problem* p) {
@@ -109,10 +108,6 @@ bdlm_status check_problem(const bdlm_problem* p) {
   if (p->clean_prefix && (reinterpret_cast<uintptr_t>(p->clean_prefix) & 3u) != 0)
     return fail(BDLM_ERR_INVALID, "clean_prefix is not 4-byte aligned");
   return BDLM_OK;
-}
-
-MaskRule host_rule(const bdlm_problem* p, const int* prefix) {
-  return MaskRule{(int)p->block_size, p->clean_intra, (int)p->window, (int)(p->L / p->block_size), (int)p->L, prefix};
 }
 
 bdlm_status check_range(const bdlm_problem* p, const bdlm_range& r, const char* what, int idx) {
@@ -213,156 +208,6 @@ QTile fwd_query_tile(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges,
   if (tiles * p->heads * p->batch <= kTeamWgs) return QTile{kQRowsShortBf16, 2};
   if (fwd_short_always(p->head_dim, p->hilo)) return QTile{kQRowsShortBf16, 1};
   return QTile{bf16_query_rows(p, n_k, k_ranges, kFwdShortWalk), 1};
-}
-
-// How the dK/dV walks of a backward are cut (SplitArgs).  A key tile's walk
-// covers the queries that see it: every query for the first clean keys, one
-// block for corrupted keys.  With few (batch, KV head, tile) workgroups the
-// longest walk, not the card, sets the kernel's time.  Walks longer than the
-// average load per CU are then cut into chunks of that length (fp32: a quarter
-// of it, as its workgroups are lighter), at least min_unit steps, below which
-// a workgroup's fixed cost and its partial sums outweigh the balance (half as
-// many where every chunk has a CU to itself: 4/2 heads, 256, 512 and 768
-// tokens, 8 -> 4 steps: 26.8 -> 21.6, 27.7 -> 24.3 and 29.3 -> 28.0 us; 1,024
-// tokens no longer fit and lose, 31.5 -> 40.4).
-// Measured: 2,040 tokens, 32/8 heads: dK/dV 375 -> 207 us, and 12 us for the
-// sums (half the average per chunk: 210 and 17); 8K, 32/4 heads, adaptive two-term products: 5.5 -> 3.4 ms (half the
-// average: 3.7); 512 tokens, 4/2 heads: 55 -> 24 us with the sums.  Calls whose
-// longest walk is within kCutSteps (or a third) of the average stay whole, as
-// cutting costs about that much (3,000 tokens, 16/16 heads: 94 steps, 75 on average: 180 us
-// cut, 167 whole; 6,000 tokens, 32/8 heads: 750 and 580: 1,157 and 1,216 us).
-struct SplitPlan {
-  SplitArgs s;
-  size_t counts_bytes = 0, bytes = 0;  // of the workspace: counts, counts + partials
-};
-constexpr int kCus = 256;
-constexpr size_t kMaxSplitBytes = (size_t)256 << 20;
-constexpr int kCutSteps = 25, kMinUnitF32 = 8, kMinUnitBf16 = 8, kMinUnitBf16Idle = 4;
-
-// Does the scheduled dK/dV kernel run this call?
-bool scheduled_dkdv(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges) {
-  int n_q_rows = 0;  // query ranges with rows (empty ones add no work to dK/dV)
-  for (int i = 0; i < n_q; ++i) n_q_rows += q_ranges[i].len > 0 ? 1 : 0;
-  return dkdv_uses_scheduled_kernel(p->dtype == BDLM_BF16, p->hilo, n_q_rows);
-}
-
-int key_tile_rows(const bdlm_problem* p) { return p->dtype == BDLM_F32 ? kRowsF32 : kBwdKeysBf16; }
-
-// Steps of the walk of the keys [first, last] of a stream (an upper bound with
-// a clean-context table, which lies in device memory: it may let every
-// corrupted query see a clean key).
-int64_t walk_steps(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges, int stream, int64_t first,
-                   int64_t last) {
-  const bool f32 = p->dtype == BDLM_F32;
-  // a step: 16 rows of one head (fp32), 32 rows of two heads, or 64 rows of one head (odd groups)
-  const int64_t group = p->heads / p->kv_heads, per_block = f32 || group % 2 ? group : group / 2;
-  const int step = f32 ? kRowsF32 : group % 2 ? 64 : 32;
-  const MaskRule rule = host_rule(p, nullptr);
-  int64_t n = 0;
-  for (int i = 0; i < n_q; ++i) {
-    const bdlm_range& qr = q_ranges[i];
-    int lo, hi, lo1, hi1;
-    query_interval(qr.stream, stream, (int)first, rule, lo, hi);
-    query_interval(qr.stream, stream, (int)last, rule, lo1, hi1);
-    if (p->clean_prefix && stream == BDLM_CLEAN && qr.stream == BDLM_CORRUPTED) {
-      lo = 0;
-      hi1 = kBig;
-    }
-    const int64_t u0 = std::max<int64_t>(lo - qr.pos0, 0), u1 = std::min<int64_t>(hi1 - qr.pos0, qr.len);
-    if (u1 > u0) n += ((u1 + step - 1) / step - u0 / step) * per_block;
-  }
-  return n;
-}
-
-// The chunks of a call's key ranges at `unit` steps each (0: whole walks).
-SplitPlan split_plan(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges, int n_k, const bdlm_range* k_ranges,
-                     int64_t unit) {
-  SplitPlan pl;
-  pl.s = SplitArgs{};
-  pl.s.unit = (int32_t)std::max<int64_t>(unit, 1);
-  const int tile = key_tile_rows(p);
-  const int64_t pairs = (int64_t)p->kv_heads * p->batch;
-  int64_t wgs = 0, slots = 0, chunked = 0;
-  for (int j = 0; j < n_k; ++j) {
-    const bdlm_range& kr = k_ranges[j];
-    const int64_t nt = (kr.len + tile - 1) / tile;
-    // walk[t] <= walk - fall t: the first tile's walk (or the longest one) and the slowest fall from it
-    int64_t walk = 0, fall = 0;
-    if (unit > 0) {
-      std::vector<int64_t> w((size_t)nt);
-      for (int64_t t = 0; t < nt; ++t) {
-        w[t] = walk_steps(p, n_q, q_ranges, kr.stream, kr.pos0 + t * tile,
-                          kr.pos0 + std::min<int64_t>((t + 1) * tile, kr.len) - 1);
-        walk = std::max(walk, w[t]);
-      }
-      fall = nt > 1 ? walk : 0;
-      for (int64_t t = 1; t < nt; ++t) fall = std::min(fall, (walk - w[t]) / t);
-    }
-    const int64_t ch = unit > 0 ? std::max<int64_t>((walk + unit - 1) / unit, 1) : 1;
-    pl.s.chunks[j] = (int32_t)ch;
-    pl.s.walk[j] = (int32_t)walk;
-    pl.s.fall[j] = (int32_t)fall;
-    wgs += nt * ch;
-    if (ch > 1) {
-      slots += slots_before(nt, walk, fall, unit);
-      chunked += nt;
-    }
-  }
-  pl.s.wgs_per_pair = (int32_t)wgs;
-  pl.s.tiles_per_pair = (int32_t)chunked;
-  pl.s.slots_per_pair = (int32_t)slots;
-  const size_t slot = (size_t)2 * tile * p->head_dim * (p->dtype == BDLM_F32 ? sizeof(double) : sizeof(float));
-  pl.counts_bytes = align256((size_t)(slots * pairs) * sizeof(int32_t));
-  pl.bytes = slots == 0 ? 0 : pl.counts_bytes + (size_t)(slots * pairs) * slot;
-  return pl;
-}
-
-// Steps per chunk (0: walks stay whole), and the workspace bytes the chunks of
-// a joint call's keys (every position of both streams) need.  The decision
-// takes the problem and its queries only, so that a key range's dK and dV do
-// not depend on which other key ranges are in the call.
-int64_t split_unit(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges, size_t* bytes) {
-  *bytes = 0;
-  const bool f32 = p->dtype == BDLM_F32;
-  if (!f32 && !scheduled_dkdv(p, n_q, q_ranges)) return 0;
-  const int tile = key_tile_rows(p);
-  const int64_t pairs = (int64_t)p->kv_heads * p->batch, tiles = (p->L + tile - 1) / tile;
-  if (tiles * pairs > 16 * kCus) return 0;  // the average over so many is what each CU gets anyway
-  int64_t total = 0, longest = 0;
-  for (int stream : {BDLM_CLEAN, BDLM_CORRUPTED})
-    for (int64_t t = 0; t < tiles; ++t) {
-      const int64_t n =
-          walk_steps(p, n_q, q_ranges, stream, t * tile, std::min<int64_t>((t + 1) * tile, p->L) - 1);
-      longest = std::max(longest, n);
-      total += n * pairs;
-    }
-  // (workgroups that fit a CU side by side: two at head_dim 64, bf16)
-  const int64_t average = total / (!f32 && p->head_dim == 64 ? 2 * kCus : kCus);
-  const bdlm_range joint[2] = {{BDLM_CLEAN, 0, 0, p->L, 0}, {BDLM_CORRUPTED, 0, 0, p->L, 0}};
-  int64_t unit = f32 ? std::max<int64_t>(kMinUnitF32, average / 4) : std::max<int64_t>(kMinUnitBf16, average);
-  if (!f32 && average < kMinUnitBf16) {
-    // a nearly idle card: shorter chunks as long as every workgroup has a CU to itself
-    const int64_t u = std::max<int64_t>(kMinUnitBf16Idle, average);
-    if (split_plan(p, n_q, q_ranges, 2, joint, u).s.wgs_per_pair * pairs <= kCus) unit = u;
-  }
-  const int64_t margin = f32 ? 0 : std::min<int64_t>(kCutSteps, average / 3);
-  for (; longest > average + margin && longest > unit; unit *= 2) {
-    *bytes = split_plan(p, n_q, q_ranges, 2, joint, unit).bytes;
-    if (*bytes <= kMaxSplitBytes) return unit;
-  }
-  *bytes = 0;
-  return 0;
-}
-
-// The row statistics' part of the backward workspace.
-size_t stats_bytes(const bdlm_problem* p, int32_t n_q, const bdlm_range* q_ranges) {
-  if (!p || !q_ranges || n_q < 1 || n_q > kMaxQ || p->batch < 1 || p->heads < 1 || p->head_dim < 1) return 0;
-  size_t tot = 0;
-  for (int i = 0; i < n_q; ++i) {
-    const size_t rows = (size_t)p->batch * (size_t)(q_ranges[i].len > 0 ? q_ranges[i].len : 0);
-    tot += 2 * align256(rows * p->heads * sizeof(float));  // LSE * log2(e), then D = rowsum(dO * O)
-  }
-  return tot;
 }
 
 bdlm_status check_grid(int64_t tiles, int64_t mult) {
@@ -503,9 +348,7 @@ size_t bdlm_attn_bwd_workspace_bytes(const bdlm_problem* p, int32_t n_q, const b
   bool ok = check_problem(p) == BDLM_OK;
   for (int i = 0; i < n_q; ++i) ok = ok && check_range(p, q_ranges[i], "query", i) == BDLM_OK;
   g_err = err;
-  size_t split = 0;
-  if (ok) split_unit(p, n_q, q_ranges, &split);
-  return base + split;
+  return ok ? base + split_plan(p, n_q, q_ranges).bytes : base;
 }
 
 }  // extern "C"
@@ -612,11 +455,11 @@ bdlm_status attn_bwd_impl(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
   if ((st = check_grid(tiles, (int64_t)p->kv_heads * p->batch)) != BDLM_OK) return st;
   a.total_tiles = (int32_t)tiles;
   // Long walks are cut when the workspace has room for the partial sums behind the row statistics.
-  size_t joint_bytes = 0;
   const size_t room = (use_scratch ? kScratchBytes : std::max(workspace_bytes, need)) - need;
-  SplitPlan plan = split_plan(p, n_q, q_ranges, n_k, k_ranges, split_unit(p, n_q, q_ranges, &joint_bytes));
-  if (plan.bytes > room) plan = split_plan(p, n_q, q_ranges, n_k, k_ranges, 0);
-  a.split = plan.s;
+  SplitPlan plan = split_plan(p, n_q, q_ranges);
+  if (plan.bytes > room) plan = SplitPlan{};
+  a.split = split_args(p, n_q, q_ranges, n_k, k_ranges, plan);
+  const bool sums = a.split.tiles_per_pair > 0;
   // The dQ kernel walks query tiles (of its own height).
   AttnArgs aq = a;
   const int dq_rows = p->dtype == BDLM_BF16 ? bf16_query_rows(p, n_k, k_ranges, kDqShortWalk) : kRowsF32;
@@ -640,7 +483,7 @@ bdlm_status attn_bwd_impl(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
     a.qr[i].l2 = aq.qr[i].l2 = l2;
     a.qr[i].delta = aq.qr[i].delta = dl;
   }
-  if (plan.bytes > 0) {
+  if (sums) {
     a.split.counts = reinterpret_cast<int32_t*>(base + need);
     a.split.partials = base + need + plan.counts_bytes;
   }
@@ -675,7 +518,7 @@ bdlm_status attn_bwd_impl(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
       for (int i = 0; i < n_q; ++i)
         if (a.qr[i].len > 0) ak.qr[ak.n_q++] = a.qr[i];
       const hipError_t le = launch_bwd_dkdv(ak, p->head_dim, stream);
-      return le != hipSuccess || plan.bytes == 0 ? le : launch_bwd_dkdv_sum(a, p->head_dim, stream);
+      return le != hipSuccess || !sums ? le : launch_bwd_dkdv_sum(a, p->head_dim, stream);
     });
     if (e != hipSuccess) return hip_fail(e, "backward dK/dV launch");
   } else {
@@ -684,7 +527,7 @@ bdlm_status attn_bwd_impl(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
     if (e != hipSuccess) return hip_fail(e, "backward dQ launch");
     e = timed(kKBwdF32, stream, [&] {
       const hipError_t le = launch_bwd_dkv_f32(a, p->head_dim, stream);
-      return le != hipSuccess || plan.bytes == 0 ? le : launch_bwd_sum_f32(a, p->head_dim, stream);
+      return le != hipSuccess || !sums ? le : launch_bwd_sum_f32(a, p->head_dim, stream);
     });
     if (e != hipSuccess) return hip_fail(e, "backward dK/dV launch");
   }

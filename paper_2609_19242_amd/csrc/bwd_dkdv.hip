@@ -270,16 +270,16 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   // This workgroup's chunk of it: steps [n0, n1).
   const int max_ch = a.split.chunks[r];
   const int nch = max_ch > 1 ? chunks_of(wp.nsteps, a.split.unit, max_ch) : 1;
-  if (max_ch > 1 && it.chunk == 0 && tid == 0) a.split.counts[it.slot] = nch;
+  if (max_ch > 1 && it.chunk == 0 && tid == 0) a.split.counts[it.tile] = nch;
   if (it.chunk >= nch) return;
   const int n0 = it.chunk * a.split.unit, n1 = it.chunk + 1 < nch ? n0 + a.split.unit : wp.nsteps;
   wp.nsteps = n1;  // (steps past the chunk copy nothing)
   // At head_dim 128 the epilogue's scalars wait in VGPRs, of which the walk
   // leaves some free (it needs every SGPR: spilled ones, read back each step,
   // cost 2% at 32K).
-  uint64_t partial_at = nch > 1 ? (uint64_t)(uintptr_t)a.split.partials +
-                                      (uint64_t)((it.slot + it.chunk) * 4 + w) * (2 * DT * 4 * 64 * 16)
-                                : 0;
+  uint64_t partial_at =
+      nch > 1 ? (uint64_t)(uintptr_t)a.split.partials + (uint64_t)partial_row<BN>(a, b, kvh, r, t, it.chunk) * (2 * D * 4)
+              : 0;
   if constexpr (D == 128) {
     asm volatile("" : "+v"(partial_at));
     // So does the walk's plan, which only the (vector) step descriptors read.
@@ -698,21 +698,25 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   const uint64_t part = ((uint64_t)__builtin_amdgcn_readfirstlane((int)(partial_at >> 32)) << 32) |
                         (uint32_t)__builtin_amdgcn_readfirstlane((int)partial_at);
   if (part != 0) {
-    // The chunk's partial sums, in register order (whole cache lines per store).
-    f32x4* pp = (f32x4*)(uintptr_t)part + lane;
+    // The chunk's partial sums: 16-byte piece 4 d + g4 of dK, then of dV, of
+    // each half, [piece][half][key], so that a store writes 512-byte runs.
+    if (key_ok) {
+      f32x4* pp = (f32x4*)(uintptr_t)part;
+      const uint32_t at = (uint32_t)(half * nk + mykey);
 #pragma unroll
-    for (int d = 0; d < DT; ++d)
+      for (int d = 0; d < DT; ++d)
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        f32x4 vk, vv;
+        for (int g4 = 0; g4 < 4; ++g4) {
+          f32x4 vk, vv;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          vk[e] = dka[d][4 * g4 + e];
-          vv[e] = dva[d][4 * g4 + e];
+          for (int e = 0; e < 4; ++e) {
+            vk[e] = dka[d][4 * g4 + e];
+            vv[e] = dva[d][4 * g4 + e];
+          }
+          pp[at + (uint32_t)((4 * d + g4) * 2 * nk)] = vk;
+          pp[at + (uint32_t)((4 * DT + 4 * d + g4) * 2 * nk)] = vv;
         }
-        pp[(4 * d + g4) * 64] = vk;
-        pp[(4 * DT + 4 * d + g4) * 64] = vv;
-      }
+    }
   } else if (a.out_f32) {
     if (key_ok) {
       const int64_t off = (((int64_t)b * kr.bstride + key0 + mykey) * HKV + kvh) * D;
@@ -779,20 +783,21 @@ __global__ __launch_bounds__(256) void dkdv_sum_kernel(const AttnArgs a) {
   constexpr int DT = D / 32, PIECES = 2 * DT * 4;  // per 32 keys: dK's 4 d + g4, then dV's
   SumItem it;
   sum_item(a, blockIdx.x / kSumWgs<D>, it);
-  const int nch = a.split.counts[it.slot];
+  const int nch = a.split.counts[blockIdx.x / kSumWgs<D>];
   if (nch <= 1) return;
   const int n = (blockIdx.x % kSumWgs<D>) * 256 + threadIdx.x;
   const int l32 = n & 31, piece = (n >> 5) % PIECES, w = (n >> 5) / PIECES;
-  const f32x4* pp = (const f32x4*)a.split.partials + (it.slot * 4 + w) * (PIECES * 64) + piece * 64 + l32;
+  const KRangeArg& kr = a.kr[it.r];
+  const int key0 = it.t * kBwdKeysBf16, nk = imin(kBwdKeysBf16, kr.len - key0);
+  if (w * 32 + l32 >= nk) return;
+  const int key = key0 + w * 32 + l32, at = piece * 2 * nk + w * 32 + l32;
   f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
   for (int ch = 0; ch < nch; ++ch) {
-    lo += pp[0];
-    hi += pp[32];
-    pp += 4 * PIECES * 64;
+    const f32x4* pp = (const f32x4*)((const float*)a.split.partials +
+                                     partial_row<kBwdKeysBf16>(a, it.b, it.kvh, it.r, it.t, ch) * (2 * D));
+    lo += pp[at];
+    hi += pp[at + nk];
   }
-  const KRangeArg& kr = a.kr[it.r];
-  const int key = it.t * kBwdKeysBf16 + w * 32 + l32;
-  if (key >= kr.len) return;
   const bool is_dv = piece >= 4 * DT;
   const float sc = is_dv ? 1.f : a.scale;
   const int64_t off = (((int64_t)it.b * kr.bstride + key) * a.kv_heads + it.kvh) * D + (piece & (4 * DT - 1)) * 8;

@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
     units += (s.t1 - s.t0) * a.group;
   }
   const int nch = a.split.chunks[it.r] > 1 ? chunks_of(units, a.split.unit, a.split.chunks[it.r]) : 1;
-  if (it.chunk == 0 && tid == 0 && a.split.chunks[it.r] > 1) a.split.counts[it.slot] = nch;
+  if (it.chunk == 0 && tid == 0 && a.split.chunks[it.r] > 1) a.split.counts[it.tile] = nch;
   if (it.chunk >= nch) return;
   const int n0 = it.chunk * a.split.unit, n1 = it.chunk + 1 < nch ? n0 + a.split.unit : units;
 
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
   }
 
   // Sum the waves through LDS, dV then dK; one chunk writes the gradients,
-  // several write fp64 partials [slot][dV, dK][key][d].
+  // several write fp64 partials [dV, dK][key][d].
   constexpr int EPT = 16 * D / (kWaves * 64);
   const int k = tid / (D / EPT), d0 = (tid % (D / EPT)) * EPT;
 #pragma unroll
@@ -297,9 +297,12 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
       for (int u = 0; u < kWaves; ++u) x[e] += lds[(u * 16 + k) * kRedRow<D> + d0 + e];
     }
     if (nch > 1) {
-      double* dst = (double*)a.split.partials + ((it.slot + it.chunk) * 2 + which) * OPS + k * D + d0;
+      double* dst = (double*)a.split.partials + partial_row<16>(a, it.b, it.kvh, it.r, it.t, it.chunk) * (2 * D) +
+                    (which * nvalid + k) * D + d0;
+      if (k < nvalid) {
 #pragma unroll
-      for (int e = 0; e < EPT; e += 2) *(f64x2*)(dst + e) = f64x2{x[e], x[e + 1]};
+        for (int e = 0; e < EPT; e += 2) *(f64x2*)(dst + e) = f64x2{x[e], x[e + 1]};
+      }
     } else if (k < nvalid) {
       float* dst = (float*)(which == 0 ? kr.dv : kr.dk) + koff + (int64_t)k * HKV * D + d0;
       const double sc = which == 0 ? 1.0 : (double)a.scale;
@@ -322,7 +325,7 @@ __global__ __launch_bounds__(256) void bwd_sum_f32_kernel(const AttnArgs a) {
   SumItem it;
   sum_item(a, blockIdx.x, it);
   const KRangeArg& kr = a.kr[it.r];
-  const int nch = a.split.counts[it.slot];
+  const int nch = a.split.counts[blockIdx.x];
   if (nch <= 1) return;
   const int nvalid = imin(16, kr.len - it.t * 16);
   const int k = threadIdx.x / (D / EPT), d0 = (threadIdx.x % (D / EPT)) * EPT;
@@ -332,7 +335,8 @@ __global__ __launch_bounds__(256) void bwd_sum_f32_kernel(const AttnArgs a) {
   for (int which = 0; which < 2; ++which) {
     double x[EPT] = {};
     for (int ch = 0; ch < nch; ++ch) {
-      const double* src = (const double*)a.split.partials + ((it.slot + ch) * 2 + which) * OPS + k * D + d0;
+      const double* src = (const double*)a.split.partials +
+                          partial_row<16>(a, it.b, it.kvh, it.r, it.t, ch) * (2 * D) + (which * nvalid + k) * D + d0;
 #pragma unroll
       for (int e = 0; e < EPT; ++e) x[e] += src[e];
     }

@@ -145,27 +145,22 @@ struct KRangeArg {
   void* dv;
 };
 
-// Long dK/dV walks cut into chunks (split_plan in api.cpp): key range r's
-// tiles are walked by up to chunks[r] workgroups, ceil(walk / unit) of them at
-// work, each of which leaves its partial sums in a slot of `partials`; a
-// second kernel adds them up in chunk order.  chunks[r] = 1: one workgroup per
-// tile, which writes the gradients itself.
+// Long dK/dV walks cut into chunks (split_plan.hpp): key range r's tiles are
+// walked by up to chunks[r] workgroups, ceil(walk / unit) of them at work, each
+// of which leaves its partial sums in `partials`; a second kernel adds them up
+// in chunk order.  chunks[r] = 1: one workgroup per tile, which writes the
+// gradients itself.
+constexpr int kMaxChunks = 64;
 struct SplitArgs {
   int32_t wgs_per_pair;    // workgroups per (batch, KV head): sum over ranges of tiles x chunks
   int32_t tiles_per_pair;  // tiles of the chunked ranges per (batch, KV head)
   int32_t unit;            // walk steps per chunk aimed at
-  int32_t slots_per_pair;  // partial slots per (batch, KV head)
-  int32_t* counts;         // chunks at work, at the slot of a tile's chunk 0
+  int32_t rows_per_pair;   // rows of partial sums (dK and dV of one key and chunk) per (batch, KV head)
+  int32_t* counts;         // chunks at work, per tile of the chunked ranges
   void* partials;
   int32_t chunks[kMaxK];
-  int32_t walk[kMaxK], fall[kMaxK];  // tile t of range r walks at most walk[r] - fall[r] t steps
+  int32_t at[2][kMaxChunks];  // chunk k's row of the key at position 0 of a stream (as if it had one)
 };
-
-// Slots of the tiles before tile t of a range: the integral of an upper bound
-// of the chunks per tile, (walk - fall t) / unit + 1.
-__host__ __device__ inline int64_t slots_before(int64_t t, int64_t walk, int64_t fall, int64_t unit) {
-  return (2 * t * (walk + unit) - fall * t * (t - 1) + 2 * unit - 1) / (2 * unit);
-}
 
 // Workgroups that share a walk of n steps: about `unit` steps each, at most max_chunks.
 __host__ __device__ inline int chunks_of(int n, int unit, int max_chunks) {

@@ -13,7 +13,7 @@ namespace bdlm {
 // at the last query row whatever the tile).
 struct KeyTileItem {
   int b, kvh, r, t, chunk;
-  int64_t slot;  // index of the tile's chunk 0 in the partials (chunked ranges)
+  int tile;  // index among the tiles of the chunked ranges of all pairs (of the tile's count)
 };
 __device__ inline bool key_tile_item(const AttnArgs& a, int wg, KeyTileItem& it) {
   int bk, rank;
@@ -21,30 +21,32 @@ __device__ inline bool key_tile_item(const AttnArgs& a, int wg, KeyTileItem& it)
   it.b = bk / a.kv_heads;
   it.kvh = bk - it.b * a.kv_heads;
   it.r = a.order[0];
-  int64_t base = 0;
+  it.tile = bk * a.split.tiles_per_pair;
   for (int n = 0; n < a.n_k; ++n) {
     const int r = a.order[n], ch = a.split.chunks[r], nw = a.kr[r].ntiles * ch;
     it.r = r;
     if (rank < nw) break;
     rank -= nw;
-    if (ch > 1) base += slots_before(a.kr[r].ntiles, a.split.walk[r], a.split.fall[r], a.split.unit);
+    if (ch > 1) it.tile += a.kr[r].ntiles;
   }
-  const int ch = a.split.chunks[it.r];
   const int nt = imax(a.kr[it.r].ntiles, 1);
   it.chunk = rank / nt;
   it.t = rank - it.chunk * nt;
-  it.slot = 0;
-  if (ch > 1)
-    it.slot = (int64_t)bk * a.split.slots_per_pair + base +
-              slots_before(it.t, a.split.walk[it.r], a.split.fall[it.r], a.split.unit);
+  it.tile += it.t;
   return true;
+}
+
+// First row of the partial sums of a chunk of key tile t (of ROWS rows) of range r.
+template <int ROWS>
+__device__ inline int64_t partial_row(const AttnArgs& a, int b, int kvh, int r, int t, int chunk) {
+  const KRangeArg& kr = a.kr[r];
+  return (int64_t)(b * a.kv_heads + kvh) * a.split.rows_per_pair + kr.pos0 + t * ROWS + a.split.at[kr.stream][chunk];
 }
 
 // A tile of the chunked ranges, for the kernel that adds up its chunks: tile
 // `n` of all pairs' chunked tiles.
 struct SumItem {
   int b, kvh, r, t;
-  int64_t slot;
 };
 __device__ inline void sum_item(const AttnArgs& a, int n, SumItem& it) {
   const int bk = n / a.split.tiles_per_pair;
@@ -52,17 +54,14 @@ __device__ inline void sum_item(const AttnArgs& a, int n, SumItem& it) {
   it.b = bk / a.kv_heads;
   it.kvh = bk - it.b * a.kv_heads;
   it.r = a.order[0];
-  it.slot = (int64_t)bk * a.split.slots_per_pair;
   for (int k = 0; k < a.n_k; ++k) {
-    const int r = a.order[k], ch = a.split.chunks[r];
+    const int r = a.order[k];
     it.r = r;
-    if (ch <= 1) continue;
+    if (a.split.chunks[r] <= 1) continue;
     if (tile < a.kr[r].ntiles) break;
     tile -= a.kr[r].ntiles;
-    it.slot += slots_before(a.kr[r].ntiles, a.split.walk[r], a.split.fall[r], a.split.unit);
   }
   it.t = tile;
-  it.slot += slots_before(tile, a.split.walk[it.r], a.split.fall[it.r], a.split.unit);
 }
 
 }  // namespace bdlm

@@ -95,3 +95,60 @@ def test_cut_walks_many_key_ranges(Hq):
         assert bool((dk[j][:, len_:] == 7.0).all()) and bool((dv[j][:, len_:] == 7.0).all())
         at += len_
     assert np.isfinite(dQ).all()
+
+
+@pytest.mark.parametrize("case", [(2660, 20, 56, 8, 128, 7, 6), (2112, 16, 16, 16, 64, 4, 3)],
+                         ids=["380-row", "528-row"])
+def test_cut_walks_do_not_depend_on_the_sharding(case):
+    """A rank's backward over ragged shards of the clean keys and over the same keys as one range: the same chunks,
+    so the same bits."""
+    L, M, Hq, Hkv, D, shards, rank = case
+    n = L // shards
+    g = torch.Generator().manual_seed(21)
+    draw = lambda rows, h: torch.randn(1, rows, h, D, generator=g).to(torch.bfloat16).to(DEV)  # noqa: E731
+    q, do, k, v = draw(n, Hq), draw(n, Hq), draw(n + L, Hkv), draw(n + L, Hkv)
+    QR = [Range(CORRUPTED, rank * n, n)]
+    p = bd.make_problem(1, L, M, Hq, Hkv, D, torch.bfloat16, out_f32=True)
+    ws = torch.empty(bd.attn_bwd_workspace_bytes(p, QR), dtype=torch.uint8, device=DEV)
+    assert ws.numel() > stats_bytes(p, QR)
+    o, lse = torch.empty(1, n, Hq, D, device=DEV), torch.empty(1, Hq, n, device=DEV)
+    own = Range(CORRUPTED, rank * n, n)
+    whole, parts = [own, Range(CLEAN, 0, L)], [own] + [Range(CLEAN, s * n, n) for s in range(shards)]
+    got = []
+    for kr in (whole, parts):
+        sizes = [r.len for r in kr]
+        split = lambda t: list(t.split(sizes, 1))  # noqa: B023, E731
+        if kr is whole:
+            bd.attn_fwd(p, QR, [q], [o], [lse], kr, split(k), split(v))
+        dq = torch.empty_like(o)
+        dk, dv = (torch.full((1, n + L, Hkv, D), 7.0, device=DEV) for _ in range(2))
+        bd.attn_bwd(p, QR, [q], [o], [lse], [do], [dq], kr, split(k), split(v), split(dk), split(dv), ws)
+        torch.cuda.synchronize()
+        got.append((dk, dv))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    dk, dv = torch.empty_like(got[0][0]), torch.empty_like(got[0][1])
+    small = torch.empty(stats_bytes(p, QR), dtype=torch.uint8, device=DEV)
+    sizes = [r.len for r in whole]
+    bd.attn_bwd(p, QR, [q], [o], [lse], [do], [torch.empty_like(o)], whole, list(k.split(sizes, 1)),
+                list(v.split(sizes, 1)), list(dk.split(sizes, 1)), list(dv.split(sizes, 1)), small)
+    torch.cuda.synchronize()
+    assert rel(got[0][0], dk) <= 1e-5 and rel(got[0][1], dv) <= 1e-5  # whole walks
+
+
+def test_noalloc_cuts_like_the_workspace_call():
+    """Partial sums that would fill more than the scratch array at the average load per chunk."""
+    L, M, H, D, B = 1080, 9, 16, 128, 2
+    q, k, v, do = (t.to(DEV) for t in joint_inputs(L, H, H, D, torch.bfloat16, batch=B, seed=31))
+    r = bd.joint_ranges(L)
+    p = bd.make_problem(B, L, M, H, H, D, torch.bfloat16)
+    assert stats_bytes(p, r) < bd.attn_bwd_workspace_bytes(p, r) <= bd.NOALLOC_SCRATCH_BYTES
+    o, lse = bd.joint_fwd(q, k, v, M)
+    want = bd.joint_bwd(q, k, v, o, lse, do, M)
+    got = tuple(torch.empty_like(t) for t in (q, k, v))
+    halves = lambda t: bd._joint_ptrs(t, L)  # noqa: E731
+    dq, dk, dv = got
+    bd.attn_bwd_noalloc(p, r, halves(q), halves(o), [lse.data_ptr(), lse.data_ptr() + L * 4], halves(do), halves(dq),
+                        r, halves(k), halves(v), halves(dk), halves(dv))
+    torch.cuda.synchronize()
+    for name, a, b in zip(("dQ", "dK", "dV"), got, want):
+        assert torch.equal(a, b), name
