@@ -335,6 +335,15 @@ inline bool dkdv_uses_scheduled_kernel(int dtype_bf16, int hilo, int n_q) {
   return dtype_bf16 && terms_ok && n_q <= 2;
 }
 
+// Workgroups of that kernel that a CU holds: two where a wave has at most 256
+// registers, at head_dim 64 but for the two-term form on odd groups (280).
+// Planned as two, that form's walks were cut too short: adaptive, head_dim 64,
+// 24/8 heads, 2K / 4K / 8K tokens 162 / 423 / 1,275 -> 152 / 407 / 1,179 us;
+// 16/16 heads, 1K / 4K 49 / 245 -> 43 / 225 (6/2 heads, 3K: 97 -> 110).
+inline int dkdv_wgs_per_cu(int head_dim, int hilo, int group) {
+  return head_dim == 64 && !((hilo & kHiloDkDv) && group % 2) ? 2 : 1;
+}
+
 // Tile heights the launchers use (the C ABI fills ntiles/tile0 with them).
 // The bf16 forward and dQ kernels take 256 query rows per workgroup (8 waves,
 // one workgroup per CU) when some row of the call can see many keys, and 128

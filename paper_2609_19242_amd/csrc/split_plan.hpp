@@ -124,8 +124,8 @@ inline SplitPlan split_plan(const bdlm_problem* p, int n_q, const bdlm_range* q_
     }
   const int64_t longest = std::max(longest_of[0], longest_of[1]);
 
-  // (workgroups that fit a CU side by side: two at head_dim 64, bf16)
-  const int64_t average = total / (!f32 && p->head_dim == 64 ? 2 * kCus : kCus);
+  const int64_t average =
+      total / (f32 ? kCus : kCus * dkdv_wgs_per_cu(p->head_dim, p->hilo, p->heads / p->kv_heads));
   int64_t unit = f32 ? std::max<int64_t>(kMinUnitF32, average / 4) : std::max<int64_t>(kMinUnitBf16, average);
   if (!f32 && average < kMinUnitBf16) {
     // a nearly idle card: shorter chunks as long as every workgroup has a CU to itself

@@ -1,4 +1,4 @@
-"""Assembly listings of the kernels built here, and two things read in them.
+"""Assembly listings of the kernels built here, and what tests read in them.
 
 f64_hazards: the result of a v_mfma_f64_16x16x4_f64 that an instruction touches
 before the matrix core has written it.  The hardware does not wait by itself on gfx950: an instruction other than a
@@ -10,6 +10,8 @@ use, nor does it know that a copy or spill of its own reads a product's result.
 scalar_offset_accesses: buffer accesses with a scalar offset.  The bounds check
 of a buffer resource leaves that offset out, so a row's address has to be in
 the vector offset for rows past the end to read as zeros.
+
+kernel_resources: the registers and LDS of each kernel.
 """
 import os
 import re
@@ -139,3 +141,12 @@ def scalar_offset_accesses(body):
         if ops[-1].split()[0] not in ("0", "null"):
             lines.append(line)
     return n, lines
+
+
+def kernel_resources(text):
+    """{kernel: {field: value}} of the numeric fields in a listing's kernel metadata."""
+    out = {}
+    for block in text.split("  - .agpr_count:")[1:]:
+        fields = dict(re.findall(r"\.(\w+):\s+(\S+)", block.split("amdhsa.target")[0]))
+        out[fields["name"]] = {k: int(v) for k, v in fields.items() if v.isdigit()}
+    return out

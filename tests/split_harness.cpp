@@ -2,7 +2,7 @@
 // stdin: "batch L block heads kv_heads head_dim fp32 intra hilo window",
 // a clean-context table "n entries...", then query and key ranges "n (stream
 // pos0 len)...".  Per call prints "unit rows_per_pair tiles_per_pair
-// counts_bytes bytes stats", then per key range "chunks ntiles" and per tile
+// counts_bytes bytes stats wgs_per_cu", then per key range "chunks ntiles" and per tile
 // its walk as the kernels count it and the first partial row of each chunk at
 // work (two or more).
 #include <cstdio>
@@ -50,8 +50,8 @@ int main() {
     p.clean_prefix = n_table ? table.data() : nullptr;
     const SplitPlan pl = split_plan(&p, (int)q.size(), q.data());
     const SplitArgs a = split_args(&p, (int)q.size(), q.data(), (int)k.size(), k.data(), pl);
-    std::printf("%lld %d %d %zu %zu %zu\n", (long long)pl.unit, a.rows_per_pair, a.tiles_per_pair, pl.counts_bytes,
-                pl.bytes, stats_bytes(&p, (int)q.size(), q.data()));
+    std::printf("%lld %d %d %zu %zu %zu %d\n", (long long)pl.unit, a.rows_per_pair, a.tiles_per_pair, pl.counts_bytes,
+                pl.bytes, stats_bytes(&p, (int)q.size(), q.data()), dkdv_wgs_per_cu(dim, hilo, heads / kv));
     const MaskRule rule = host_rule(&p, p.clean_prefix);
     const int tile = key_tile_rows(&p), group = heads / kv;
     const int bm = f32 ? kRowsF32 : group % 2 ? 64 : 32, per = f32 || group % 2 ? group : group / 2;

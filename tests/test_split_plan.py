@@ -5,12 +5,14 @@ are divided, and the chunks of a walk do not depend on that division.  Host
 code, run on the CPU; the walks are counted as the kernels count them."""
 import os
 import random
+import re
 import shutil
 import subprocess
 
 import pytest
 
 import paper_2609_19242_amd as bd
+from tests.asm_listing import kernel_resources, listing
 from paper_2609_19242_amd import CLEAN, CORRUPTED
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -38,7 +40,7 @@ def harness(tmp_path_factory):
         lines = iter(subprocess.run([exe], input=inp, capture_output=True, text=True, check=True).stdout.split("\n"))
         out = []
         for c in calls:
-            keys = ("unit", "rows", "tiles", "counts_bytes", "bytes", "stats")
+            keys = ("unit", "rows", "tiles", "counts_bytes", "bytes", "stats", "wgs_per_cu")
             r = dict(zip(keys, map(int, next(lines).split())), ranges=[])
             for s, pos0, n in c["k"]:
                 head, *tiles = next(lines).split(" | ")
@@ -158,3 +160,23 @@ def test_the_size_query_holds_the_plan(harness):
                             clean_intra=c["intra"], hilo=c["hilo"], window=c["window"])
         n = bd.attn_bwd_workspace_bytes(p, [bd.Range(*x) for x in c["q"]])
         assert n == r["stats"] + (r["bytes"] if r["unit"] else 0), c
+
+
+def test_workgroups_per_cu_are_those_of_the_kernels(harness):
+    """The planner's side-by-side workgroups against the registers and LDS of the kernels as built."""
+    text = listing("bwd_dkdv.hip")
+    if text is None:
+        pytest.skip("hipcc not available")
+    seen = 0
+    for name, res in kernel_resources(text).items():
+        m = re.search(r"dkdv_kernelILi(\d+)ELb(\d)ELb(\d)E", name)
+        if not m:
+            continue
+        D, adaptive, rows = (int(x) for x in m.groups())
+        waves_per_simd = 512 // (-(-res["vgpr_count"] // 8) * 8)  # a workgroup has one wave on each SIMD
+        held = min(waves_per_simd, 160 * 1024 // res["group_segment_fixed_size"])
+        c = dict(batch=1, L=256, M=16, H=3 if rows else 2, KV=1, D=D, f32=0, intra=0, hilo=15 if adaptive else 0,
+                 window=0, table=[], q=[(CLEAN, 0, 256)], k=[(CLEAN, 0, 256)])
+        assert harness([c])[0]["wgs_per_cu"] == held, (name, res)
+        seen += 1
+    assert seen == 8
