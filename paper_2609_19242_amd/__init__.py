@@ -156,6 +156,16 @@ def _stream(stream) -> int:
     return stream.cuda_stream
 
 
+def _torch_stream(stream, device) -> torch.cuda.Stream:
+    """The torch stream of a ``stream`` argument (a torch stream or a raw handle) on ``device``."""
+    if isinstance(stream, torch.cuda.Stream):
+        return stream
+    handle = _stream(stream)
+    if handle == 0:  # the default stream, for which ExternalStream would take one from torch's pool
+        return torch.cuda.default_stream(device)
+    return torch.cuda.ExternalStream(handle, device=device)
+
+
 def _dtype_code(dt: torch.dtype) -> int:
     if dt == torch.bfloat16:
         return BF16
@@ -423,7 +433,7 @@ def joint_bwd(q, k, v, o, lse, do, block_size: int, clean_intra: int = CLEAN_INT
         nbytes = lib().bdlm_attn_bwd_workspace_bytes(ctypes.byref(p), 2, r)
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=q.device)
         if stream is not None:  # used on that stream after this call has dropped it
-            workspace.record_stream(torch.cuda.ExternalStream(_stream(stream), device=q.device))
+            workspace.record_stream(_torch_stream(stream, q.device))
     else:
         nbytes = workspace.numel() * workspace.element_size()
     nq, nk, eq, eo = L * Hq * D, L * k.shape[2] * D, q.element_size(), o.element_size()
