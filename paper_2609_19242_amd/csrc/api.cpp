@@ -131,10 +131,6 @@ bdlm_status check_ptr(const void* ptr, const char* what, int idx) {
   return BDLM_OK;
 }
 
-float resolved_scale(const bdlm_problem* p) {
-  return p->scale > 0.f ? p->scale : 1.0f / std::sqrt((float)p->head_dim);
-}
-
 void fill_common(AttnArgs& a, const bdlm_problem* p) {
   a = AttnArgs{};
   a.batch = (int32_t)p->batch;

@@ -1,5 +1,6 @@
 // dK and dV of the BDLM attention backward, key-major, bf16 inputs, fp32 accumulation, gfx950: the general
-// kernel, for calls with more than two query ranges or two-term products on every step (bwd_dkdv.hip has the rest).
+// kernel, for calls with more than two query ranges, two-term products on every step or a tiny scale (bwd_dkdv.hip has
+// the rest).
 //
 // Exact gradients from the saved O and LSE (arXiv 2609.19242 App. C fused
 // backward; eq:correctness-corrupted-gradient and eq:correctness-clean-gradient):
@@ -586,17 +587,12 @@ void launch_nh(const AttnArgs& a, int n, hipStream_t s) {
     hipLaunchKernelGGL((bwd_bf16_kernel<D, HM, 1, NQ>), dim3(n), dim3(256), 0, s, a);
 }
 
-// (single-term and adaptive products of at most two query ranges run in bwd_dkdv.hip)
+// (single-term and adaptive products of at most two query ranges come here at
+// tiny scales only, dkdv_uses_scheduled_kernel: no form of their own)
 template <int D, int HM>
 hipError_t launch_nq(const AttnArgs& a, int n, hipStream_t s) {
-  if constexpr (HM == 1) {
-    if (a.n_q <= 2) {
-      launch_nh<D, HM, 2>(a, n, s);
-      return hipGetLastError();
-    }
-  }
-  if (a.n_q <= 2) return hipErrorInvalidValue;
-  launch_nh<D, HM, kMaxQ>(a, n, s);
+  if (HM == 1 && a.n_q <= 2) launch_nh<D, 1, 2>(a, n, s);
+  else launch_nh<D, HM, kMaxQ>(a, n, s);
   return hipGetLastError();
 }
 

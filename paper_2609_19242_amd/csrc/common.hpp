@@ -329,10 +329,12 @@ __host__ __device__ inline WalkStep walk_step(const WalkPlan& w, int i) {
 // products, at most two query ranges with rows) starts its score and dP
 // accumulators at -LSE/scale and -D, so the backward workspace holds those
 // (stats form 1); the general kernel of bwd_bf16.hip and the fp32 kernel read
-// LSE log2(e) and D (form 0).
-inline bool dkdv_uses_scheduled_kernel(int dtype_bf16, int hilo, int n_q) {
+// LSE log2(e) and D (form 0).  The general kernel also takes scales so small
+// that LSE/scale could pass the fp32 range.
+constexpr float kMinScheduledScale = 0x1p-96f;
+inline bool dkdv_uses_scheduled_kernel(int dtype_bf16, int hilo, int n_q, float scale) {
   const bool terms_ok = !(hilo & kHiloDkDv) || (hilo & kHiloAdaptive);
-  return dtype_bf16 && terms_ok && n_q <= 2;
+  return dtype_bf16 && terms_ok && n_q <= 2 && scale >= kMinScheduledScale;
 }
 
 // Workgroups of that kernel that a CU holds: two where a wave has at most 256

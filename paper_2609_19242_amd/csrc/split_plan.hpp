@@ -5,6 +5,7 @@
 #include "bdlm_attn.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstddef>
 
 #include "common.hpp"
@@ -28,11 +29,15 @@ inline size_t stats_bytes(const bdlm_problem* p, int32_t n_q, const bdlm_range* 
   return tot;
 }
 
+inline float resolved_scale(const bdlm_problem* p) {
+  return p->scale > 0.f ? p->scale : 1.0f / std::sqrt((float)p->head_dim);
+}
+
 // Does the scheduled dK/dV kernel run this call?
 inline bool scheduled_dkdv(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges) {
   int n_q_rows = 0;  // query ranges with rows (empty ones add no work to dK/dV)
   for (int i = 0; i < n_q; ++i) n_q_rows += q_ranges[i].len > 0 ? 1 : 0;
-  return dkdv_uses_scheduled_kernel(p->dtype == BDLM_BF16, p->hilo, n_q_rows);
+  return dkdv_uses_scheduled_kernel(p->dtype == BDLM_BF16, p->hilo, n_q_rows, resolved_scale(p));
 }
 
 inline int key_tile_rows(const bdlm_problem* p) { return p->dtype == BDLM_F32 ? kRowsF32 : kBwdKeysBf16; }
