@@ -696,6 +696,18 @@ __global__ __launch_bounds__(256) void dkdv_kernel(const AttnArgs a) {
   // ---- epilogue: dK = scale dK^T^T, dV (bf16 or fp32); unseen keys get zeros
 #pragma unroll
   for (int d = 0; d < DT; ++d) asm volatile("" : "+a"(dka[d]), "+a"(dva[d]));
+  // A key that no query sees keeps zeros whatever its rows hold: a non-finite K
+  // or V row makes NaN of its hidden pairs.
+  const bool unseen = (R0.qw | R1.qw) == 0;
+  if (__builtin_amdgcn_ballot_w64(unseen) != 0) {
+#pragma unroll
+    for (int d = 0; d < DT; ++d)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        dka[d][i] = unseen ? 0.f : dka[d][i];
+        dva[d][i] = unseen ? 0.f : dva[d][i];
+      }
+  }
   const uint64_t part = ((uint64_t)__builtin_amdgcn_readfirstlane((int)(partial_at >> 32)) << 32) |
                         (uint32_t)__builtin_amdgcn_readfirstlane((int)partial_at);
   if (part != 0) {
