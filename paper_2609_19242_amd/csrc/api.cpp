@@ -196,8 +196,9 @@ int bf16_query_rows(const bdlm_problem* p, int n_k, const bdlm_range* k_ranges, 
 }
 
 // Query tile of the bf16 forward: 128 rows shared by two teams when the call
-// has few such tiles (a choice by the queries alone, so that a row's sums are
-// the same whichever key ranges are in the call).
+// has few such tiles.  (The number of teams depends on the queries alone.  A
+// key tile's team, and so the grouping of a row's sums, depends on the number
+// of visible tiles before it, those of other key ranges included.)
 QTile fwd_query_tile(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges, int n_k, const bdlm_range* k_ranges) {
   int64_t tiles = 0;
   for (int i = 0; i < n_q; ++i) tiles += (q_ranges[i].len + kQRowsShortBf16 - 1) / kQRowsShortBf16;

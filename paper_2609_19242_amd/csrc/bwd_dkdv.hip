@@ -29,9 +29,9 @@
 //      step's accumulator starts, and its first row reads (issued before the
 //      step's barrier: that stage is complete from the barrier before)
 // Row operands are read four products ahead, transpose operands eight (at
-// head_dim 64 two and four: at most 252 registers, so two workgroups share a
-// CU; the two-term form on odd groups takes 280 and runs alone).  The
-// walk's bookkeeping is vector work: the descriptors of 64 steps (block,
+// head_dim 64 two and four, in the two-term forms one and two: at most 252
+// registers, so two workgroups share a CU; the two-term form on odd groups
+// takes 280 and runs alone).  The walk's bookkeeping is vector work: the descriptors of 64 steps (block,
 // range, partial flag, copy resource words) sit in the lanes of a few VGPRs,
 // computed every 56 steps from a closed form (walk_plan, walk_step), and a
 // step reads its own with readlane, so a step issues about 27 scalar

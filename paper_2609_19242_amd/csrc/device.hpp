@@ -142,15 +142,6 @@ __device__ __forceinline__ float exp2f_fast(float x) { return __builtin_amdgcn_e
 
 __device__ __forceinline__ bf16 to_bf16(float x) { return (bf16)x; }
 
-}  // namespace bdlm
-
-namespace bdlm {
-// fp32 atomic add through a buffer resource: offsets past the resource's end
-// are dropped by the hardware, so callers need no per-lane bounds branch.
-__device__ __forceinline__ void buf_atomic_add(__amdgpu_buffer_rsrc_t r, uint32_t byte_off, float v) {
-  __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(v, r, byte_off, 0, 0);
-}
-
 // A wave's 32 rows x D columns held the MFMA-accumulator way (the lanes l32
 // and l32 + 32 own row l32; element e of fragment (dt, g4) is column
 // 32 dt + 8 g4 + 4 half + e), written to global memory as bf16 through the

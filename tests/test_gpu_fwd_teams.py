@@ -3,6 +3,9 @@ tiles) against the fp64 oracle: one key tile and several (team 1 idle, odd and
 even tile counts), ragged rows, rows that see no key, several key ranges, both
 head dims and all three forms of P; and the one-team form at the other side of
 the limit."""
+import os
+import re
+
 import pytest
 import torch
 
@@ -11,14 +14,28 @@ import paper_2609_19242_amd as bd
 from paper_2609_19242_amd import CLEAN, CORRUPTED, Range
 from tests.gpu_util import assert_close, joint_inputs
 
-pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
-# L, block, heads, kv_heads, batch, window; the last two have 256 and 258 tiles
+# L, block, heads, kv_heads, batch, window
 SHAPES = [(32, 8, 2, 1, 1, 0), (70, 10, 4, 2, 2, 0), (200, 25, 2, 2, 1, 30), (513, 27, 2, 1, 1, 0),
-          (1024, 64, 16, 2, 1, 0), (129, 3, 43, 1, 2, 0)]
+          (1024, 64, 16, 2, 1, 0), (258, 3, 43, 1, 1, 0), (129, 3, 43, 1, 2, 0)]
+CSRC = os.path.join(os.path.dirname(os.path.abspath(bd.__file__)), "csrc")
 
 
+def query_tiles(shape):
+    """128-row query tiles of the call: two ranges of L rows."""
+    L, _, Hq, _, B, _ = shape
+    return 2 * -(-L // 128) * Hq * B
+
+
+def test_shapes_reach_both_sides_of_the_limit():
+    limit = int(re.search(r"kTeamWgs = (\d+);", open(os.path.join(CSRC, "common.hpp")).read()).group(1))
+    tiles = [query_tiles(s) for s in SHAPES]
+    assert limit == 256 and max(t for t in tiles if t <= limit) == limit, tiles
+    assert min(t for t in tiles if t > limit) == limit + 2, tiles  # two equal ranges: an even count
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("hilo", [0, bd.HILO_ALL, bd.HILO_ALL | bd.HILO_ADAPTIVE], ids=["single", "two", "adaptive"])
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
@@ -32,6 +49,7 @@ def test_forward_teams(shape, D, hilo):
     assert_close(f"{shape} d{D} LSE", lse[:, heads], LSE, torch.bfloat16)
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("D", [64, 128])
 def test_partials_with_empty_rows(D):
     """Clean shards of 90 keys: rows of the first blocks see none of the later ones (O = 0, LSE = -inf), and

@@ -107,8 +107,9 @@ def test_two_terms_amplified_keys(reading, hilo, Hq):
     probability on one key) with two-term products on every tile and on the adaptive
     selection: batch 1, L = 2048 + 2048, block 128, Hq/2 heads, d 128, every row and
     key against the oracle with fp32 outputs.  Both branches of the adaptive test run:
-    tiles with a large probability and tiles without one; an even GQA group takes the
-    scheduled dK/dV kernel, an odd one the general kernel."""
+    tiles with a large probability and tiles without one; the adaptive form runs the
+    scheduled dK/dV kernel, in steps of two heads (even GQA group) or of 64 rows of one
+    head (odd), the other form the general kernel."""
     import synth
     L, M, Hkv, D = 2048, 128, 2, 128
     q = synth.normal((1, 2 * L, Hq, D), 9100, torch.bfloat16)
