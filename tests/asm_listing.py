@@ -1,11 +1,13 @@
 """Assembly listings of the kernels built here, and what tests read in them.
 
-f64_hazards: the result of a v_mfma_f64_16x16x4_f64 that an instruction touches
-before the matrix core has written it.  The hardware does not wait by itself on gfx950: an instruction other than a
-product of the same accumulator (same destination, as its addend) must come at
-least 19 wait states after the product, along every path.  The compiler pads
-builtin products, but cannot see into the inline assembly that the fp32 kernels
-use, nor does it know that a copy or spill of its own reads a product's result.
+product_hazards: the result of a matrix product in inline assembly that an
+instruction touches before the matrix core has written it.  The hardware does
+not wait by itself on gfx950: an instruction other than a product of the same
+accumulator (same destination, as its addend) must come at least 19 wait states
+after a v_mfma_f64_16x16x4_f64 and 12 after a v_mfma_f32_32x32x16_bf16, along
+every path.  The compiler pads builtin products, but cannot see into inline
+assembly, nor does it know that a copy or spill of its own reads a product's
+result.
 
 scalar_offset_accesses: buffer accesses with a scalar offset.  The bounds check
 of a buffer resource leaves that offset out, so a row's address has to be in
@@ -17,8 +19,8 @@ import os
 import re
 import subprocess
 
-WAIT = 19  # wait states between a 16x16x4 fp64 product and a read (or another write) of its result
-PRODUCT = "v_mfma_f64_16x16x4_f64"
+F64, BF16 = "v_mfma_f64_16x16x4_f64", "v_mfma_f32_32x32x16_bf16"
+WAIT = {F64: 19, BF16: 12}  # wait states between a product and a read (or another write) of its result
 _CACHE = {}
 
 
@@ -74,8 +76,11 @@ def functions(listing):
     return out
 
 
-def f64_hazards(body):
-    """[(line of the use, line of the product, wait states between)] of one function, over all its paths."""
+def product_hazards(body, product=F64, accumulators="v"):
+    """[(line of the use, line of the product, wait states between)] of one function, over all its paths, for the
+    products whose accumulators are in the given register file."""
+    wait = WAIT[product]
+    ours = lambda op, ops: op == product and ops[0].startswith(accumulators)  # noqa: E731
     at_label = {lab: i for i, (_, lab, _, _) in enumerate(body) if lab}
     found = {}
     # state: register -> (wait states still missing, line of the product); worklist over instruction indices
@@ -97,7 +102,7 @@ def f64_hazards(body):
                 i += 1
                 continue
             touched = set()
-            if op == PRODUCT:
+            if ours(op, ops):
                 dst, addend = _regs(ops[0]), _regs(ops[3])
                 touched = set(_regs(ops[1]) | _regs(ops[2]))
                 if dst != addend:
@@ -110,16 +115,16 @@ def f64_hazards(body):
                 for o in ops:
                     touched |= _regs(o)
             for r in touched & state.keys():
-                missing, product = state[r]
-                key = (line, product)
+                missing, at = state[r]
+                key = (line, at)
                 found[key] = max(found.get(key, 0), missing)
             passed = 1
             if op == "s_nop":
                 passed = int(ops[0], 0) + 1
             state = {r: (v[0] - passed, v[1]) for r, v in state.items() if v[0] > passed}
-            if op == PRODUCT:
+            if ours(op, ops):
                 for r in _regs(ops[0]):
-                    state[r] = (WAIT, line)
+                    state[r] = (wait, line)
             if op in ("s_endpgm", "s_setpc_b64"):
                 break
             if op == "s_branch":
@@ -128,7 +133,7 @@ def f64_hazards(body):
             if op.startswith("s_cbranch"):
                 work.append((at_label[ops[0]], dict(state)))
             i += 1
-    return sorted((use, product, WAIT - missing) for (use, product), missing in found.items())
+    return sorted((use, at, wait - missing) for (use, at), missing in found.items())
 
 
 def scalar_offset_accesses(body):
