@@ -38,11 +38,11 @@ constexpr double kLn2D = 0.69314718055994530942;
 __device__ __forceinline__ void mfma64(f64x4& c, double a, double b) {
   asm volatile("s_nop 1\n\tv_mfma_f64_16x16x4_f64 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
-// Before vector code reads c: its last product must have left the matrix core
-// (19 wait states).  The compiler does not see the product in the inline
-// assembly: any use of c that it may add, a copy or a spill included, has to
-// come after this too.
-__device__ __forceinline__ void mfma64_done(f64x4& c) { asm volatile("s_nop 15\n\ts_nop 7" : "+v"(c)); }
+// Before vector code reads results of mfma64: the last product must have left
+// the matrix core (19 wait states).  The compiler does not see the product in
+// the inline assembly: any use of a result that it may add, a copy or a spill
+// included, has to come after such a wait too.
+#define BDLM_F64_WAIT "s_nop 15\n\ts_nop 2"
 
 // Sum (or any reduction) partners of a C-layout column: lanes i, i+16, i+32, i+48.
 __device__ __forceinline__ double shfl_d(double x, int src) {
@@ -130,8 +130,7 @@ __device__ __forceinline__ f64x4 row_product(const fl4 (&x)[D / 16], const doubl
     mfma64(c0, (double)x[c][2], q[c & 1][1][0]);
     mfma64(c1, (double)x[c][3], q[c & 1][1][1]);
   }
-  mfma64_done(c0);
-  mfma64_done(c1);
+  asm volatile(BDLM_F64_WAIT : "+v"(c0), "+v"(c1));
   return c0 + c1;
 }
 
@@ -195,10 +194,10 @@ struct AccTiles {
   // Before vector code reads the accumulators (one wait for all of them).
   __device__ __forceinline__ void done() {
     if constexpr (D == 128)
-      asm volatile("s_nop 15\n\ts_nop 7"
+      asm volatile(BDLM_F64_WAIT
                    : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(t[4]), "+v"(t[5]), "+v"(t[6]), "+v"(t[7]));
     else
-      asm volatile("s_nop 15\n\ts_nop 7" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]));
+      asm volatile(BDLM_F64_WAIT : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]));
   }
   __device__ __forceinline__ void scale(double s) {
     done();
