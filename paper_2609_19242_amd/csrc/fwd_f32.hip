@@ -15,7 +15,7 @@
 // Bound by the fp64 matrix rate, on small problems by the walk's latency.
 // Measured against one thread per row with a serial fp64 chain per key:
 // L = 256, 2/2 heads, d 64: 402 -> 17 us; L = 1125, 8/2 heads, d 128: 6.1 ms
-// -> 0.15 ms (35 TFLOP/s).
+// -> 0.15 ms (35 TFLOP/s).  (At head_dim 128 six VGPRs are spilled.)
 // Output: normalised O and natural-log LSE; a row that sees no key gets O = 0
 // and LSE = -inf.
 #include "f64tile.hpp"

@@ -44,7 +44,8 @@ inline int key_tile_rows(const bdlm_problem* p) { return p->dtype == BDLM_F32 ? 
 
 // Steps of the walk of the keys [first, last] of a stream (an upper bound with
 // a clean-context table, which lies in device memory: it may let every
-// corrupted query see a clean key).
+// corrupted query see a clean key.  The decision to cut takes the bound too, so
+// a drafter's clean walks look all alike and are cut less than they could be).
 inline int64_t walk_steps(const bdlm_problem* p, int n_q, const bdlm_range* q_ranges, int stream, int64_t first,
                           int64_t last) {
   const bool f32 = p->dtype == BDLM_F32;
